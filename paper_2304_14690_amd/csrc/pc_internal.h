@@ -107,7 +107,13 @@ struct pc_geom {
                     // (negative) for a block that wraps around a periodic axis
   int64_t ms;       // stride of the node coefficient streams: M rounded up
                     // to 64, so that every stream starts on a 512-byte line
-  double* ncoef;    // [d][bn][ms]
+  // fit = m_node where a node's rows are evaluated from its position
+  // (pc_stencil.h: k_node fills the block of 3 or 4 lines per axis): no node
+  // coefficients are kept, xyz holds the node positions.  0: stored rows.
+  int fit;
+  double hsup, eps; // support radius, Eq. 17's shape parameter
+  double* xyz;      // [d][ms] or null
+  double* ncoef;    // [d][bn][ms] or null
   float* ncoef32;   // [d][bn][ms] or null
   // IB lists
   int32_t* ib;          // [n_ib] node index
@@ -125,7 +131,8 @@ struct pc_geom {
   // compact node stencils of the B+V nodes; ibs = n_ib rounded up to 64
   int64_t ibs;
   int32_t* ibbase;      // [n_ib]
-  double* ibcoef;       // [d][bn][ibs]
+  double* ibx;          // [d][ibs] positions (fit) or null
+  double* ibcoef;       // [d][bn][ibs] or null
   float* ibcoef32;
   // node-to-node stencils of the first fractional step (k_self = 0: none):
   // neighbour node sidx [k_self][ms] (ascending), coefficients

@@ -1,0 +1,277 @@
+// WLS derivative rows evaluated where they are applied (Sec. 2.2, Eqs. 9-17),
+// instead of read back from stored coefficients.
+//
+// Node targets with a full block of m^d grid points (m = 3 or 4).  The block
+// is a tensor product of grid lines and the Gaussian weight of Eq. 17 a
+// product over the axes, so the weighted fit of Eq. 16 is diagonal in
+// products of the discrete orthogonal polynomials of each axis: with
+// w_l = exp(-beta t_l^2) on the m lines of an axis (t in grid spacings),
+// p0 = 1, p1, p2 monic and orthogonal under w, the products p_i p_j p_k of
+// total degree <= 2 span the same space as Eq. 16's polynomial vector and
+// are orthogonal under the product weight.  The fitted gradient at the node
+// (p' the derivative, all at the node; <.> over the lines of an axis) is then
+//   d/dx = <E>_x <A0>_y <A0>_z + <A1>_x <p1 A1>_y <A0>_z + <A1>_x <A0>_y <p1 A1>_z
+// with A_i = w p_i / <w p_i p_i> and E = A1 + p2' A2, and likewise for the
+// other axes: the coefficients that C^-1 A of Eq. 13 gives, without the
+// normal matrix.  A node costs about 500 float64 operations in 3D and its
+// position instead of 648 bytes of coefficients.
+#pragma once
+
+#include "pc_internal.h"
+
+namespace pc {
+
+// 1/x for normal x: the hardware reciprocal and two Newton steps.
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+
+// exp(y) for y <= 709 (flushed to exp(-700) below -700): y = k ln 2 + r,
+// |r| <= ln 2 / 2, and a degree-11 polynomial in r (the minimax fit of
+// (exp(r) - 1 - r) / r^2 leaves 1.3e-17 of the result).
+__device__ __forceinline__ double exp_fast(double y) {
+  constexpr double LOG2E = 1.4426950408889634074, MAGIC = 6755399441055744.0;  // 1.5 2^52
+  constexpr double LN2 = 6.9314718055994530942e-1, LN2_LO = 2.3190468138462995584e-17;
+  y = fmax(y, -700.0);
+  const double t = __builtin_fma(y, LOG2E, MAGIC);
+  const double k = t - MAGIC;
+  double r = __builtin_fma(-k, LN2, y);
+  r = __builtin_fma(-k, LN2_LO, r);
+  double p = 2.5100385495510319078e-8;
+  p = __builtin_fma(p, r, 2.7620088445409748161e-7);
+  p = __builtin_fma(p, r, 2.7557268459997064772e-6);
+  p = __builtin_fma(p, r, 2.4801521295954375131e-5);
+  p = __builtin_fma(p, r, 1.9841269863053616878e-4);
+  p = __builtin_fma(p, r, 1.3888888917213716901e-3);
+  p = __builtin_fma(p, r, 8.3333333333300618325e-3);
+  p = __builtin_fma(p, r, 4.1666666666624127873e-2);
+  p = __builtin_fma(p, r, 1.6666666666666667453e-1);
+  p = __builtin_fma(p, r, 5.0000000000000010221e-1);
+  p = __builtin_fma(p, r, 1.0);
+  p = __builtin_fma(p, r, 1.0);
+  // the low word of t is k: add it to the exponent
+  const uint64_t tb = __builtin_bit_cast(uint64_t, t), pb = __builtin_bit_cast(uint64_t, p);
+  const uint32_t hi = (uint32_t)(pb >> 32) + ((uint32_t)tb << 20);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)pb);
+}
+
+// ---- node targets ---------------------------------------------------------------
+// What the rows of a node need besides its position and block corner.
+struct NodeFit {
+  int32_t n[3];
+  int per;               // bit a: axis a is periodic
+  double off;            // grid point i at (i + off) h
+  double h[3], ih[3];
+  double hl[3];          // half the box length
+  double inv_n0, inv_n1;
+  double hsup2, eps;     // squared support radius, Eq. 17's shape parameter
+  double beta[3], s[3];  // eps h^2 / hsup^2 and exp(-beta) per axis
+};
+
+NodeFit node_fit_args(const pc_geom* g);
+
+// One axis of a node's fit: the vectors A0, A1 and E above over the block's
+// lines and p1 at the node, in units of the grid spacing.
+template <int MB>
+struct AxisFit {
+  double a0[MB], a1[MB], e[MB], p1;
+  double W, N1, N2;  // <w>, <w p1 p1>, <w p2 p2> (the pivots of the normal matrix)
+};
+
+// t1: offset of the block's second line from the node in grid spacings (line
+// l sits at y = l - 1, the node at y = -t1); beta and s as in NodeFit.  The
+// weights are taken relative to the second line's (a common factor cancels).
+template <int MB>
+__device__ __forceinline__ AxisFit<MB> axis_fit(double t1, double beta, double s) {
+  static_assert(MB == 3 || MB == 4, "block lines");
+  AxisFit<MB> F;
+  const double up = exp_fast(2.0 * beta * t1), dn = recip(up);
+  const double w0 = s * up, w2 = s * dn, ys = -t1;
+  if constexpr (MB == 3) {
+    const double sum = w0 + w2, W = sum + 1.0, iW = recip(W);
+    const double a = (w2 - w0) * iW;
+    const double q0 = -1.0 - a, q1 = -a, q2 = 1.0 - a;
+    const double v0 = w0 * q0, v1 = q1, v2 = w2 * q2;
+    const double N1 = __builtin_fma(v0, q0, __builtin_fma(v1, q1, v2 * q2)), iN = recip(N1);
+    F.a0[0] = w0 * iW; F.a0[1] = iW; F.a0[2] = w2 * iW;
+    F.a1[0] = v0 * iN; F.a1[1] = v1 * iN; F.a1[2] = v2 * iN;
+    // w p2 is proportional to (1, -2, 1), the only vector orthogonal to the
+    // linear functions on three lines: A2 = (1, -2, 1) / 2
+    const double c = __builtin_fma(2.0, ys, -(F.a1[0] + F.a1[2]));  // p2' at the node
+    const double hc = 0.5 * c;
+    F.e[0] = F.a1[0] + hc; F.e[1] = F.a1[1] - c; F.e[2] = F.a1[2] + hc;
+    F.p1 = ys - a;
+    F.W = W; F.N1 = N1; F.N2 = 4.0 / (1.0 / w0 + 4.0 + 1.0 / w2);
+  } else {
+    const double s2 = s * s, w3 = (s2 * s2) * (dn * dn);
+    const double W = ((w0 + w2) + w3) + 1.0, iW = recip(W);
+    const double a = __builtin_fma(2.0, w3, w2 - w0) * iW;
+    const double q[4] = {-1.0 - a, -a, 1.0 - a, 2.0 - a};
+    const double w[4] = {w0, 1.0, w2, w3}, y2[4] = {1.0, 0.0, 1.0, 4.0};
+    double v[4], N1 = 0.0, b = 0.0;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      v[l] = w[l] * q[l];
+      N1 = __builtin_fma(v[l], q[l], N1);
+      b = __builtin_fma(v[l], y2[l], b);
+    }
+    const double iN = recip(N1);
+    b *= iN;
+    const double d = (w0 + w2 + 4.0 * w3) * iW;  // <w y^2> / <w>
+    double u[4], N2 = 0.0;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      F.a0[l] = w[l] * iW;
+      F.a1[l] = v[l] * iN;
+      const double p2 = __builtin_fma(-b, q[l], y2[l]) - d;
+      u[l] = w[l] * p2;
+      N2 = __builtin_fma(u[l], p2, N2);
+    }
+    const double c = __builtin_fma(2.0, ys, -b) * recip(N2);  // p2' at the node over <w p2 p2>
+#pragma unroll
+    for (int l = 0; l < 4; ++l) F.e[l] = __builtin_fma(c, u[l], F.a1[l]);
+    F.p1 = ys - a;
+    F.W = W; F.N1 = N1; F.N2 = N2;
+  }
+  return F;
+}
+
+// The block of a node: low corner per axis (on a periodic axis the wrapped
+// line) and the fit of every axis.  kappa (nullable): h / h_t per axis.
+template <int D, int MB>
+struct BlockFit {
+  int c[3];
+  AxisFit<MB> ax[D];
+};
+
+template <int D, int MB>
+__device__ __forceinline__ BlockFit<D, MB> block_fit(const NodeFit& A, int32_t base,
+                                                     const double (&x)[D],
+                                                     double* kappa2 = nullptr) {
+  BlockFit<D, MB> B;
+  // flat index to lines: (c + 1/2) / n0 lies at least 1/(2 n0) from an
+  // integer, far above the rounding of its float64 product
+  const int flat = base < 0 ? ~base : base;
+  int q = (int)(((double)flat + 0.5) * A.inv_n0);
+  B.c[0] = flat - q * A.n[0];
+  B.c[1] = q;
+  B.c[2] = 0;
+  if (D == 3) {
+    const int z = (int)(((double)q + 0.5) * A.inv_n1);
+    B.c[1] = q - z * A.n[1];
+    B.c[2] = z;
+  }
+  double x1[D], rk2 = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    double x0 = ((double)B.c[a] + A.off) * A.h[a] - x[a];
+    // a block that starts one box length back (periodic axis)
+    const int back = (((A.per >> a) & 1) && x0 > A.hl[a]) ? A.n[a] : 0;
+    x0 = ((double)(B.c[a] - back) + A.off) * A.h[a] - x[a];
+    x1[a] = ((double)(B.c[a] - back + 1) + A.off) * A.h[a] - x[a];
+    const double xe = ((double)(B.c[a] - back + MB - 1) + A.off) * A.h[a] - x[a];
+    rk2 += fmax(x0 * x0, xe * xe);
+  }
+  double beta[D], s[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    beta[a] = A.beta[a];
+    s[a] = A.s[a];
+  }
+  // h_t = max(support, the farthest block point): beyond the support radius
+  // only next to a wall, or with a support below the block's
+  const double ht2 = fmax(rk2, A.hsup2);
+  if (rk2 > A.hsup2) {
+    const double er = A.eps / rk2;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      beta[a] = er * (A.h[a] * A.h[a]);
+      s[a] = exp_fast(-beta[a]);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    if (kappa2) kappa2[a] = A.h[a] * A.h[a] / ht2;
+    B.ax[a] = axis_fit<MB>(x1[a] * A.ih[a], beta[a], s[a]);
+  }
+  return B;
+}
+
+// Offset of line l of axis a's block from its low corner, in lines; a line
+// past the end of a periodic axis is one box length back.
+template <bool WRAP>
+__device__ __forceinline__ int line_off(const NodeFit& A, int a, int c, int l) {
+  return WRAP && ((A.per >> a) & 1) && c + l >= A.n[a] ? l - A.n[a] : l;
+}
+
+// grad f at a node from f on its block; rd(l, j, k) reads line (l, j, k).
+template <int D, int MB, typename RD>
+__device__ __forceinline__ void block_grad(const NodeFit& A, const BlockFit<D, MB>& B,
+                                           const RD& rd, double (&G)[D]) {
+  const AxisFit<MB>& X = B.ax[0];
+  const AxisFit<MB>& Y = B.ax[1];
+  if constexpr (D == 2) {
+    double gx = 0.0, gy = 0.0, xb = 0.0, yb = 0.0;
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+      double s0 = 0.0, s1 = 0.0, se = 0.0;
+#pragma unroll
+      for (int l = 0; l < MB; ++l) {
+        const double f = rd(l, j, 0);
+        s0 = __builtin_fma(X.a0[l], f, s0);
+        s1 = __builtin_fma(X.a1[l], f, s1);
+        se = __builtin_fma(X.e[l], f, se);
+      }
+      gx = __builtin_fma(Y.a0[j], se, gx);
+      xb = __builtin_fma(Y.a1[j], s1, xb);
+      gy = __builtin_fma(Y.e[j], s0, gy);
+    }
+    G[0] = __builtin_fma(Y.p1, xb, gx) * A.ih[0];
+    G[1] = __builtin_fma(X.p1, xb, gy) * A.ih[1];
+  } else {
+    const AxisFit<MB>& Z = B.ax[2];
+    double gx = 0.0, gy = 0.0, gz = 0.0, hx = 0.0, hy = 0.0;
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+      double pe0 = 0.0, p10 = 0.0, p11 = 0.0, p00 = 0.0, p01 = 0.0, p0e = 0.0;
+#pragma unroll
+      for (int j = 0; j < MB; ++j) {
+        double s0 = 0.0, s1 = 0.0, se = 0.0;
+#pragma unroll
+        for (int l = 0; l < MB; ++l) {
+          const double f = rd(l, j, k);
+          s0 = __builtin_fma(X.a0[l], f, s0);
+          s1 = __builtin_fma(X.a1[l], f, s1);
+          se = __builtin_fma(X.e[l], f, se);
+        }
+        pe0 = __builtin_fma(Y.a0[j], se, pe0);
+        p10 = __builtin_fma(Y.a0[j], s1, p10);
+        p11 = __builtin_fma(Y.a1[j], s1, p11);
+        p00 = __builtin_fma(Y.a0[j], s0, p00);
+        p01 = __builtin_fma(Y.a1[j], s0, p01);
+        p0e = __builtin_fma(Y.e[j], s0, p0e);
+      }
+      gx = __builtin_fma(Z.a0[k], __builtin_fma(Y.p1, p11, pe0), gx);
+      gy = __builtin_fma(Z.a0[k], __builtin_fma(X.p1, p11, p0e), gy);
+      hx = __builtin_fma(Z.a1[k], p10, hx);
+      hy = __builtin_fma(Z.a1[k], p01, hy);
+      gz = __builtin_fma(Z.e[k], p00, gz);
+    }
+    G[0] = __builtin_fma(Z.p1, hx, gx) * A.ih[0];
+    G[1] = __builtin_fma(Z.p1, hy, gy) * A.ih[1];
+    G[2] = __builtin_fma(X.p1, hx, __builtin_fma(Y.p1, hy, gz)) * A.ih[2];
+  }
+}
+
+// The coefficient of block point (l, j, k) in every component of the
+// gradient (for inspection; the transfers apply the factors directly).
+template <int D, int MB>
+__device__ __forceinline__ void block_coef(const NodeFit& A, const BlockFit<D, MB>& B, int l, int j,
+                                           int k, double (&c)[D]) {
+  auto rd = [&](int a, int b, int d) { return a == l && b == j && d == k ? 1.0 : 0.0; };
+  block_grad<D, MB>(A, B, rd, c);
+}
+
+}  // namespace pc

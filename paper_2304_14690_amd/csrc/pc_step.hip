@@ -20,8 +20,30 @@
 #include <mutex>
 
 #include "pc_internal.h"
+#include "pc_stencil.h"
 
 namespace pc {
+
+NodeFit node_fit_args(const pc_geom* g) {
+  NodeFit A;
+  std::memset(&A, 0, sizeof(A));
+  A.per = g->per;
+  A.off = g->vertex ? 0.0 : 0.5;
+  A.eps = g->eps;
+  A.hsup2 = g->hsup * g->hsup;
+  for (int a = 0; a < 3; ++a) {
+    A.n[a] = a < g->d ? g->n[a] : 1;
+    A.h[a] = g->h[a];
+    A.ih[a] = 1.0 / g->h[a];
+    A.hl[a] = 0.5 * (double)A.n[a] * g->h[a];
+    A.beta[a] = g->eps * (g->h[a] * g->h[a]) / A.hsup2;
+    A.s[a] = std::exp(-A.beta[a]);
+  }
+  A.inv_n0 = 1.0 / A.n[0];
+  A.inv_n1 = 1.0 / A.n[1];
+  return A;
+}
+
 namespace {
 
 constexpr int XCDS = 8;
@@ -365,15 +387,88 @@ __global__ void __launch_bounds__(TPB) k_grad_all(const int32_t* __restrict__ nb
   }
 }
 
+// The same from the nodes' positions (geometries with a full block of MB
+// lines per axis, pc_stencil.h).  With stored rows the gradient streamed 256
+// (2D) or 648 (3D) bytes of float64 coefficients per node; from positions it
+// reads 20 or 28, and is bound by the fields, the positions and about 500
+// float64 operations (3D) together.  With the projection, float64:
+// 512 x 256 x 256 (33.6M nodes) 4.70 -> 0.74 ms, 2048^2 231 -> 60 us; the B+V
+// step at 512 x 256 x 256 45 -> 15 us.  Float32 fields use the same float64
+// rows and sums: 200 x 168 x 120 241 -> 86 us.
+template <typename T, int D, int MB, bool WRAP>
+__device__ __forceinline__ void fit_grad(const NodeFit& A, int32_t b32, const double (&x)[D],
+                                         const T* __restrict__ phi, double (&G)[D]) {
+  const BlockFit<D, MB> B = block_fit<D, MB>(A, b32, x);
+  const int64_t base = b32 < 0 ? ~b32 : b32;
+  const int64_t plane = (int64_t)A.n[0] * A.n[1];
+  // the block's values first, all in flight during the fit
+  T f[D == 3 ? MB : 1][MB][MB];
+#pragma unroll
+  for (int k = 0; k < (D == 3 ? MB : 1); ++k) {
+    const int64_t bz = base + (D == 3 ? line_off<WRAP>(A, 2, B.c[2], k) * plane : 0);
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+      const int64_t by = bz + (int64_t)line_off<WRAP>(A, 1, B.c[1], j) * A.n[0];
+#pragma unroll
+      for (int l = 0; l < MB; ++l) f[k][j][l] = phi[by + line_off<WRAP>(A, 0, B.c[0], l)];
+    }
+  }
+  block_grad<D, MB>(A, B, [&](int l, int j, int k) { return (double)f[k][j][l]; }, G);
+}
+
+template <typename T, int D, int MB, bool PROJECT, bool WRAP>
+__global__ void __launch_bounds__(TPB) k_grad_fit(const int32_t* __restrict__ nbase,
+                                                  const double* __restrict__ xyz, int64_t M,
+                                                  int64_t ms, NodeFit A,
+                                                  const T* __restrict__ phi, double scale,
+                                                  const T* __restrict__ u,
+                                                  T* __restrict__ out,
+                                                  const int32_t* __restrict__ skip) {
+  if (skip && *skip) return;
+  const int64_t n = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
+  if (n >= M) return;
+  const int32_t b32 = ldnt(nbase + n);
+  double x[D], G[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) x[a] = ldnt(xyz + a * ms + n);
+  T uu[D];
+  if (PROJECT) {
+#pragma unroll
+    for (int a = 0; a < D; ++a) uu[a] = ldnt(u + a * M + n);
+  }
+  fit_grad<T, D, MB, WRAP>(A, b32, x, phi, G);
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    if (PROJECT)
+      __builtin_nontemporal_store((T)((double)uu[a] - scale * G[a]), out + a * M + n);
+    else
+      out[a * M + n] = (T)(scale * G[a]);
+  }
+}
+
 // ---- grad at the B+V nodes (compact stencils) ---------------------------------
+template <typename T, int D, int MB>
+__global__ void __launch_bounds__(TPB) k_grad_ib_fit(const int32_t* __restrict__ ibbase,
+                                                     const double* __restrict__ ibx, int64_t nib,
+                                                     int64_t ibs, NodeFit A,
+                                                     const T* __restrict__ phi,
+                                                     T* __restrict__ out) {
+  const int64_t s = (int64_t)blockIdx.x * TPB + threadIdx.x;
+  if (s >= nib) return;
+  double x[D], G[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) x[a] = ibx[a * ibs + s];
+  fit_grad<T, D, MB, true>(A, ibbase[s], x, phi, G);
+#pragma unroll
+  for (int a = 0; a < D; ++a) out[a * nib + s] = (T)G[a];
+}
+
 template <typename T, int D, bool LOCALREF>
 __global__ void __launch_bounds__(TPB) k_grad_ib(const int32_t* __restrict__ ibbase,
                                                  const T* __restrict__ ibcoef, int64_t nib,
                                                  int64_t ibs, int bn,
                                                  BlockOffsets bo, const T* __restrict__ phi,
-                                                 T scale, T* __restrict__ out,
-                                                 const int32_t* __restrict__ skip) {
-  if (skip && *skip) return;
+                                                 T* __restrict__ out) {
   const int64_t s = (int64_t)blockIdx.x * TPB + threadIdx.x;
   if (s >= nib) return;
   const int32_t b32 = ibbase[s];
@@ -391,7 +486,7 @@ __global__ void __launch_bounds__(TPB) k_grad_ib(const int32_t* __restrict__ ibb
     for (int a = 0; a < D; ++a) acc[a] += ibcoef[((int64_t)a * bn + o) * ibs + s] * f;
   }
 #pragma unroll
-  for (int a = 0; a < D; ++a) out[a * nib + s] = scale * acc[a];
+  for (int a = 0; a < D; ++a) out[a * nib + s] = acc[a];
 }
 
 // ---- gathers / scatters on the IB list ------------------------------------------
@@ -522,45 +617,64 @@ __global__ void __launch_bounds__(TPB) k_ib_finish(const double* __restrict__ pa
 // iteration's RHS update near the IB.  (A last-block-finishes scheme needs a
 // device-scope fence and an atomic per block, which cost more than a second
 // launch here.)
-template <typename T, int D, int BN>
+// MB > 0: the rows from the nodes' positions ibx (pc_stencil.h); 0: from
+// the stored coefficients.
+template <typename T, int D, int BN, int MB>
 __global__ void __launch_bounds__(IBT) k_ib_step(const int32_t* __restrict__ ibbase,
-                                                 const T* __restrict__ ibcoef, int64_t nib,
-                                                 int64_t ibs, int bnrt,
-                                                 BlockOffsets bo, const T* __restrict__ phi,
+                                                 const T* __restrict__ ibcoef,
+                                                 const double* __restrict__ ibx, int64_t nib,
+                                                 int64_t ibs, int bnrt, BlockOffsets bo, NodeFit A,
+                                                 const T* __restrict__ phi,
                                                  T scale, const T* __restrict__ uib,
                                                  T* __restrict__ g, double* __restrict__ part,
                                                  const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
-  const int bn = BN > 0 ? BN : bnrt;
   const int64_t s = (int64_t)blockIdx.x * IBT + threadIdx.x;
   double num = 0.0, den = 0.0;
   if (s < nib) {
     const int32_t b32 = ibbase[s];
-    const int64_t base = b32 >= 0 ? b32 : ~b32;  // ~corner: the block wraps
-    const BlockWrap w = block_wrap(base, bo);
-    constexpr int MB = BN == 16 && D == 2 ? 4 : (BN == 27 && D == 3 ? 3 : 0);
-    const int m = MB > 0 ? MB : bo.m;
-    T acc[D];
+    T ug[D], go[D], gr[D];
 #pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = T(0);
-    const bool lr = sizeof(T) == 4;
-    T ref = lr ? phi[base + bo.off[0]] : T(0);
+    for (int a = 0; a < D; ++a) {
+      ug[a] = uib[a * nib + s];
+      go[a] = g[a * nib + s];
+    }
+    if constexpr (MB > 0) {
+      double x[D], G[D];
 #pragma unroll
-    for (int o = 0; o < (BN > 0 ? BN : PC_MAX_K_NODE); ++o) {
-      if (o < bn) {
-        T f = phi[wrap_adjust(base + bo.off[o], o % m, (o / m) % m, o / (m * m), w, bo)];
-        if (lr) f -= ref;
+      for (int a = 0; a < D; ++a) x[a] = ibx[a * ibs + s];
+      fit_grad<T, D, MB, true>(A, b32, x, phi, G);
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] += ibcoef[((int64_t)a * bn + o) * ibs + s] * f;
+      for (int a = 0; a < D; ++a) gr[a] = (T)((double)scale * G[a]);
+    } else {
+      const int bn = BN > 0 ? BN : bnrt;
+      const int64_t base = b32 >= 0 ? b32 : ~b32;  // ~corner: the block wraps
+      const BlockWrap w = block_wrap(base, bo);
+      constexpr int ML = BN == 16 && D == 2 ? 4 : (BN == 27 && D == 3 ? 3 : 0);
+      const int m = ML > 0 ? ML : bo.m;
+      T acc[D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) acc[a] = T(0);
+      const bool lr = sizeof(T) == 4;
+      T ref = lr ? phi[base + bo.off[0]] : T(0);
+#pragma unroll
+      for (int o = 0; o < (BN > 0 ? BN : PC_MAX_K_NODE); ++o) {
+        if (o < bn) {
+          T f = phi[wrap_adjust(base + bo.off[o], o % m, (o / m) % m, o / (m * m), w, bo)];
+          if (lr) f -= ref;
+#pragma unroll
+          for (int a = 0; a < D; ++a) acc[a] += ibcoef[((int64_t)a * bn + o) * ibs + s] * f;
+        }
       }
+#pragma unroll
+      for (int a = 0; a < D; ++a) gr[a] = scale * acc[a];
     }
     double mn = 0.0, mo = 0.0;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      T gn = -uib[a * nib + s] + scale * acc[a];
-      T go = g[a * nib + s];
+      T gn = -ug[a] + gr[a];
       mn += (double)gn * (double)gn;
-      mo += (double)go * (double)go;
+      mo += (double)go[a] * (double)go[a];
       g[a * nib + s] = gn;
     }
     double dm = sqrt(mn) - sqrt(mo);
@@ -775,8 +889,27 @@ template <typename T, bool PROJECT>
 int launch_grad_all(const pc_geom* g, const T* ncoef, const T* phi, T scale, const T* u, T* out,
                     hipStream_t s, const int32_t* skip = nullptr) {
   const bool lr = sizeof(T) == 4;
-  BlockOffsets bo = block_offsets(g);
   dim3 grid(nblk(g->M)), block(TPB);
+  if (g->fit) {
+    const NodeFit nf = node_fit_args(g);
+#define GRF(D, MB, W)                                                                            \
+  hipLaunchKernelGGL((k_grad_fit<T, D, MB, PROJECT, W>), grid, block, 0, s, g->nbase, g->xyz,    \
+                     g->M, g->ms, nf, phi, (double)scale, u, out, skip)
+#define GRM(D)                                                    \
+  do {                                                            \
+    if (g->fit == 3) {                                            \
+      if (g->per) GRF(D, 3, true); else GRF(D, 3, false);         \
+    } else {                                                      \
+      if (g->per) GRF(D, 4, true); else GRF(D, 4, false);         \
+    }                                                             \
+  } while (0)
+    if (g->d == 2) GRM(2); else GRM(3);
+#undef GRM
+#undef GRF
+    PC_HIP_CHECK(hipGetLastError());
+    return PC_OK;
+  }
+  BlockOffsets bo = block_offsets(g);
 #define GRW(D, BN, W)                                                                           \
   do {                                                                                          \
     if (lr)                                                                                     \
@@ -805,26 +938,39 @@ int launch_grad_all(const pc_geom* g, const T* ncoef, const T* phi, T scale, con
 }
 
 template <typename T>
-int launch_grad_ib(const pc_geom* g, const T* ibcoef, const T* phi, T scale, T* out,
-                   hipStream_t s, const int32_t* skip = nullptr) {
+int launch_grad_ib(const pc_geom* g, const T* ibcoef, const T* phi, T* out, hipStream_t s) {
   if (g->n_ib == 0) return PC_OK;
   const bool lr = sizeof(T) == 4;
-  BlockOffsets bo = block_offsets(g);
   dim3 grid(nblk(g->n_ib)), block(TPB);
+  if (g->fit) {
+    const NodeFit nf = node_fit_args(g);
+#define GIF(D, MB)                                                                            \
+  hipLaunchKernelGGL((k_grad_ib_fit<T, D, MB>), grid, block, 0, s, g->ibbase, g->ibx, g->n_ib, \
+                     g->ibs, nf, phi, out)
+    if (g->d == 2) {
+      if (g->fit == 3) GIF(2, 3); else GIF(2, 4);
+    } else {
+      if (g->fit == 3) GIF(3, 3); else GIF(3, 4);
+    }
+#undef GIF
+    PC_HIP_CHECK(hipGetLastError());
+    return PC_OK;
+  }
+  BlockOffsets bo = block_offsets(g);
   if (g->d == 2) {
     if (lr)
       hipLaunchKernelGGL((k_grad_ib<T, 2, true>), grid, block, 0, s, g->ibbase, ibcoef, g->n_ib,
-                         g->ibs, g->bn, bo, phi, scale, out, skip);
+                         g->ibs, g->bn, bo, phi, out);
     else
       hipLaunchKernelGGL((k_grad_ib<T, 2, false>), grid, block, 0, s, g->ibbase, ibcoef, g->n_ib,
-                         g->ibs, g->bn, bo, phi, scale, out, skip);
+                         g->ibs, g->bn, bo, phi, out);
   } else {
     if (lr)
       hipLaunchKernelGGL((k_grad_ib<T, 3, true>), grid, block, 0, s, g->ibbase, ibcoef, g->n_ib,
-                         g->ibs, g->bn, bo, phi, scale, out, skip);
+                         g->ibs, g->bn, bo, phi, out);
     else
       hipLaunchKernelGGL((k_grad_ib<T, 3, false>), grid, block, 0, s, g->ibbase, ibcoef, g->n_ib,
-                         g->ibs, g->bn, bo, phi, scale, out, skip);
+                         g->ibs, g->bn, bo, phi, out);
   }
   PC_HIP_CHECK(hipGetLastError());
   return PC_OK;
@@ -861,15 +1007,22 @@ int launch_ib_step(const pc_geom* g, const T* ibcoef, const T* phi, T scale, con
                    const int32_t* skip, int32_t* host_flag, double* host_sums, bool close = true) {
   if (g->n_ib == 0) return PC_OK;
   BlockOffsets bo = block_offsets(g);
+  const NodeFit nf = node_fit_args(g);
   dim3 grid((unsigned)((g->n_ib + IBT - 1) / IBT)), block(IBT);
   // flag[0]: converged, flag[1]: iterations
-#define IBS(D, BN)                                                                              \
-  hipLaunchKernelGGL((k_ib_step<T, D, BN>), grid, block, 0, s, g->ibbase, ibcoef, g->n_ib, g->ibs, \
-                     g->bn, bo, phi, scale, uib, gib, part, skip)
+#define IBS(D, BN, MB)                                                                          \
+  hipLaunchKernelGGL((k_ib_step<T, D, BN, MB>), grid, block, 0, s, g->ibbase, ibcoef, g->ibx,    \
+                     g->n_ib, g->ibs, g->bn, bo, nf, phi, scale, uib, gib, part, skip)
   if (g->d == 2) {
-    if (g->bn == 16) IBS(2, 16); else IBS(2, 0);
+    if (g->fit == 4) IBS(2, 0, 4);
+    else if (g->fit == 3) IBS(2, 0, 3);
+    else if (g->bn == 16) IBS(2, 16, 0);
+    else IBS(2, 0, 0);
   } else {
-    if (g->bn == 27) IBS(3, 27); else IBS(3, 0);
+    if (g->fit == 3) IBS(3, 0, 3);
+    else if (g->fit == 4) IBS(3, 0, 4);
+    else if (g->bn == 27) IBS(3, 27, 0);
+    else IBS(3, 0, 0);
   }
 #undef IBS
   if (close)
@@ -1365,8 +1518,8 @@ int pc_grad_to_nodes(const pc_geom* g, int dtype, const void* phi, void* grad, i
   }
   if (subset == PC_IB) {
     if (dtype == PC_F64)
-      return launch_grad_ib<double>(g, g->ibcoef, (const double*)phi, 1.0, (double*)grad, s);
-    return launch_grad_ib<float>(g, g->ibcoef32, (const float*)phi, 1.0f, (float*)grad, s);
+      return launch_grad_ib<double>(g, g->ibcoef, (const double*)phi, (double*)grad, s);
+    return launch_grad_ib<float>(g, g->ibcoef32, (const float*)phi, (float*)grad, s);
   }
   return fail(PC_ERR_INVALID_ARG, "subset must be PC_ALL or PC_IB");
 }

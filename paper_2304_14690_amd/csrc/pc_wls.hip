@@ -26,6 +26,7 @@
 #include <cstring>
 
 #include "pc_internal.h"
+#include "pc_stencil.h"
 
 namespace pc {
 namespace {
@@ -755,6 +756,118 @@ __global__ void __launch_bounds__(64) k_node_stencils(NodeStencilArgs A) {
   }
 }
 
+// Geometries whose node rows are evaluated from positions (pc_stencil.h): the
+// block corners, the positions in a stream-aligned copy, and the singularity
+// test.  In the order of Eq. 16's terms the pivots of the normal matrix are
+// the squared norms of the products p_i p_j p_k (halved for the squares,
+// scaled by (h / h_t)^(2 (i + j + k))).
+template <int D, int MB>
+__global__ void __launch_bounds__(256) k_node_fit(const double* __restrict__ xyz, int64_t M,
+                                                  GridDesc g, NodeFit A,
+                                                  int32_t* __restrict__ nbase,
+                                                  double* __restrict__ xo, int64_t ms,
+                                                  int32_t* __restrict__ bad) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n >= M) return;
+  double x[D];
+  int64_t flat0 = 0, stride = 1;
+  bool wraps = false;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    x[a] = xyz[a * M + n];
+    xo[a * ms + n] = x[a];
+    double lo = floor(x[a] / g.h[a] - (0.5 * MB - 1.0 + g.off));
+    if (!((g.per >> a) & 1)) lo = fmin(fmax(lo, 0.0), (double)(g.n[a] - MB));
+    const int b = (int)lo, na = g.n[a];
+    wraps = wraps || b < 0 || b + MB > na;
+    flat0 += (int64_t)(b < 0 ? b + na : b) * stride;
+    stride *= na;
+  }
+  const int32_t base = wraps ? ~(int32_t)flat0 : (int32_t)flat0;
+  nbase[n] = base;
+  double k2[D];
+  const BlockFit<D, MB> B = block_fit<D, MB>(A, base, x, k2);
+  double all = 1.0, pmin = 1e300, pmax = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) all *= B.ax[a].W;
+  bool pos = all > 0.0;
+  auto pivot = [&](double p) {
+    pos = pos && p > 0.0;
+    pmin = fmin(pmin, p);
+    pmax = fmax(pmax, p);
+  };
+  pivot(all);
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const double ra = all / B.ax[a].W * k2[a];
+    pivot(ra * B.ax[a].N1);
+    pivot(0.25 * ra * k2[a] * B.ax[a].N2);
+#pragma unroll
+    for (int b = 0; b < a; ++b)
+      pivot(ra * B.ax[a].N1 * (B.ax[b].N1 / B.ax[b].W) * k2[b]);
+  }
+  if (!(pos && pmin / pmax >= SINGULAR_RATIO)) atomicOr(bad, 1);
+}
+
+// Coefficients of the nodes nds[t] (null: node t), component a of block
+// point o at (a * bn + o) * os + t (for inspection).
+template <int D, int MB>
+__global__ void __launch_bounds__(64) k_fit_export(const int32_t* __restrict__ nbase,
+                                                   const double* __restrict__ xyz, int64_t M,
+                                                   int64_t ms, NodeFit A,
+                                                   const int64_t* __restrict__ nds, int64_t nn,
+                                                   double* __restrict__ out, int64_t os,
+                                                   int32_t* __restrict__ bad) {
+  const int64_t t = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (t >= nn) return;
+  const int64_t n = nds ? nds[t] : t;
+  if (n < 0 || n >= M) {
+    if (bad) *bad = 1;
+    return;
+  }
+  double x[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) x[a] = xyz[a * ms + n];
+  const BlockFit<D, MB> B = block_fit<D, MB>(A, nbase[n], x);
+  constexpr int BN = D == 2 ? MB * MB : MB * MB * MB;
+  for (int o = 0; o < BN; ++o) {
+    double c[D];
+    block_coef<D, MB>(A, B, o % MB, (o / MB) % MB, o / (MB * MB), c);
+#pragma unroll
+    for (int a = 0; a < D; ++a) out[((int64_t)a * BN + o) * os + t] = c[a];
+  }
+}
+
+int launch_fit_export(const pc_geom* g, const int64_t* nds, int64_t nn, double* out, int64_t os,
+                      int32_t* bad, hipStream_t s) {
+  if (nn == 0) return PC_OK;
+  const NodeFit nf = node_fit_args(g);
+#define FEX(D, MB)                                                                              \
+  hipLaunchKernelGGL((k_fit_export<D, MB>), dim3((unsigned)((nn + 63) / 64)), dim3(64), 0, s,    \
+                     g->nbase, g->xyz, g->M, g->ms, nf, nds, nn, out, os, bad)
+  if (g->d == 2) {
+    if (g->fit == 3) FEX(2, 3); else FEX(2, 4);
+  } else {
+    if (g->fit == 3) FEX(3, 3); else FEX(3, 4);
+  }
+#undef FEX
+  PC_HIP_CHECK(hipGetLastError());
+  return PC_OK;
+}
+
+// Positions of the IB nodes and their block corners, gathered compact.
+__global__ void __launch_bounds__(256) k_ib_positions(const int32_t* __restrict__ ib, int64_t nib,
+                                                      int d, const int32_t* __restrict__ nbase,
+                                                      const double* __restrict__ xyz, int64_t ms,
+                                                      int64_t ibs, int32_t* __restrict__ ibbase,
+                                                      double* __restrict__ ibx) {
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (s >= nib) return;
+  const int64_t n = ib[s];
+  ibbase[s] = nbase[n];
+  for (int a = 0; a < d; ++a) ibx[a * ibs + s] = xyz[a * ms + n];
+}
+
 // ---- node-to-node stencils (the first fractional step) ------------------------------
 // Eq. 11 polynomial vector of the known-value form (2D: x, y, x^2/2, xy, y^2/2;
 // 3D: x, y, z, x^2/2, xy, xz, y^2/2, yz, z^2/2) of scaled offsets.
@@ -983,7 +1096,7 @@ __global__ void __launch_bounds__(256) k_export_at(const int32_t* __restrict__ g
         const int32_t v = nbase[n];
         obase[t] = v < 0 ? ~v : v;
       }
-      if (oncoef)
+      if (oncoef && ncoef)
         for (int r = 0; r < d * bn; ++r) oncoef[(int64_t)r * nn + t] = ncoef[(int64_t)r * ms + n];
     }
   }
@@ -1009,7 +1122,7 @@ void geom_free(pc_geom* g) {
   void* ptrs[] = {g->gidx,   g->gcoef,  g->gcoef32, g->nbase,  g->ncoef,  g->ncoef32,
                   g->ib,     g->near,   g->nslot,   g->ncoefib, g->ncoefib32, g->ibbase,
                   g->ibcoef, g->ibcoef32, g->sidx,  g->scoef,   g->scoef32,  g->vlist,
-                  g->perm};
+                  g->perm,   g->xyz,    g->ibx};
   for (void* p : ptrs) dev_free(p);
 }
 
@@ -1027,7 +1140,7 @@ struct Scratch {
 
 // Device bytes held by a geometry with these counts (the arrays of
 // pc_wls_build; the node permutation of PC_ORDER_CELL not included).
-int64_t geom_bytes_for(int d, int64_t G, int64_t M, int k_grid, int bn, int64_t n_ib,
+int64_t geom_bytes_for(int d, int64_t G, int64_t M, int k_grid, int bn, bool fit, int64_t n_ib,
                        int64_t n_near, int near_w, bool want64, bool want32, int k_self,
                        int64_t n_v) {
   const int64_t ms = (M + 63) / 64 * 64, ibs = (n_ib + 63) / 64 * 64;
@@ -1035,14 +1148,21 @@ int64_t geom_bytes_for(int d, int64_t G, int64_t M, int k_grid, int bn, int64_t 
   // indices, bases and lists (every geometry)
   int64_t bytes = (int64_t)k_grid * G * 4 + M * 4 + n_ib * 4 + n_near * 4 + ell * 4 +
                   n_ib * 4 + (int64_t)k_self * ms * 4 + n_v * 4;
+  if (fit) bytes += (int64_t)d * (ms + ibs) * 8;  // positions
   // coefficients, per kept precision (s bytes a value)
   for (int s : {8, 4}) {
     if (!(s == 8 ? want64 : want32)) continue;
-    bytes += ((int64_t)d * k_grid * G + (int64_t)d * bn * ms + ell * d + ibs * (int64_t)d * bn +
+    bytes += ((int64_t)d * k_grid * G + (fit ? 0 : (int64_t)d * bn * (ms + ibs)) + ell * d +
               (int64_t)k_self * ms * (d + 1)) * s;
   }
   return bytes;
 }
+
+// Block lines per axis of a geometry that evaluates its node rows from
+// positions, or 0 where it keeps them: the block has to be a full tensor
+// product (k_node = m^d), and the kernels are written for the blocks of the
+// default stencils (4^2, 3^3) and their 3^2 and 4^3 neighbours.
+int fit_lines(int k_node, int bn, int m) { return k_node == bn && (m == 3 || m == 4) ? m : 0; }
 
 // The stencil copies a build keeps, from pc_wls_opts.dtype_mask: bit
 // (1 << PC_F64) float64, bit (1 << PC_F32) float32; 0 means float64 only.
@@ -1234,16 +1354,33 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   // node-target stencils
   PC_TRY(dev_alloc((void**)&g->nbase, (size_t)M * 4, "node stencil bases"));
   g->ms = (M + 63) / 64 * 64;
-  if (want64)
-    PC_TRY(dev_alloc((void**)&g->ncoef, (size_t)d * bn * g->ms * 8, "node stencil coefficients"));
-  if (want32)
-    PC_TRY(dev_alloc((void**)&g->ncoef32, (size_t)d * bn * g->ms * 4, "node stencil f32"));
-  NodeStencilArgs na{xyz, M, gd, m, bn, k_node, eps, support * delta, g->nbase, g->ms, g->ncoef,
-                     g->ncoef32, bad};
-  if (d == 2)
-    hipLaunchKernelGGL(k_node_stencils<2>, dim3(nblocks(M, 64)), dim3(64), 0, s, na);
-  else
-    hipLaunchKernelGGL(k_node_stencils<3>, dim3(nblocks(M, 64)), dim3(64), 0, s, na);
+  g->fit = fit_lines(k_node, bn, m);
+  g->hsup = support * delta;
+  g->eps = eps;
+  if (g->fit) {
+    PC_TRY(dev_alloc((void**)&g->xyz, (size_t)d * g->ms * 8, "node positions"));
+    const NodeFit nf = node_fit_args(g);
+#define NFL(D, MB)                                                                            \
+  hipLaunchKernelGGL((k_node_fit<D, MB>), dim3(nblocks(M, 256)), dim3(256), 0, s, xyz, M, gd, nf, \
+                     g->nbase, g->xyz, g->ms, bad)
+    if (d == 2) {
+      if (m == 3) NFL(2, 3); else NFL(2, 4);
+    } else {
+      if (m == 3) NFL(3, 3); else NFL(3, 4);
+    }
+#undef NFL
+  } else {
+    if (want64)
+      PC_TRY(dev_alloc((void**)&g->ncoef, (size_t)d * bn * g->ms * 8, "node stencil coefficients"));
+    if (want32)
+      PC_TRY(dev_alloc((void**)&g->ncoef32, (size_t)d * bn * g->ms * 4, "node stencil f32"));
+    NodeStencilArgs na{xyz, M, gd, m, bn, k_node, eps, support * delta, g->nbase, g->ms, g->ncoef,
+                       g->ncoef32, bad};
+    if (d == 2)
+      hipLaunchKernelGGL(k_node_stencils<2>, dim3(nblocks(M, 64)), dim3(64), 0, s, na);
+    else
+      hipLaunchKernelGGL(k_node_stencils<3>, dim3(nblocks(M, 64)), dim3(64), 0, s, na);
+  }
   PC_HIP_CHECK(hipGetLastError());
 
   // node-to-node stencils (the first fractional step)
@@ -1344,14 +1481,19 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   }
   if (g->n_ib) {
     PC_TRY(dev_alloc((void**)&g->ibbase, (size_t)g->n_ib * 4, "IB bases"));
+    if (g->fit) {
+      PC_TRY(dev_alloc((void**)&g->ibx, (size_t)d * g->ibs * 8, "IB positions"));
+      hipLaunchKernelGGL(k_ib_positions, dim3(nblocks(g->n_ib, 256)), dim3(256), 0, s, g->ib,
+                         g->n_ib, d, g->nbase, g->xyz, g->ms, g->ibs, g->ibbase, g->ibx);
+    }
     // the first gather also writes the bases
-    if (want64) {
+    if (!g->fit && want64) {
       PC_TRY(dev_alloc((void**)&g->ibcoef, (size_t)d * bn * g->ibs * 8, "IB coefs"));
       hipLaunchKernelGGL(k_ib_gather<double>, dim3(nblocks(g->n_ib, 256)), dim3(256), 0, s,
                          g->ib, g->n_ib, g->nbase, g->ncoef, g->ms, d * bn, g->ibs, g->ibbase,
                          g->ibcoef);
     }
-    if (want32) {
+    if (!g->fit && want32) {
       PC_TRY(dev_alloc((void**)&g->ibcoef32, (size_t)d * bn * g->ibs * 4, "IB coefs"));
       hipLaunchKernelGGL(k_ib_gather<float>, dim3(nblocks(g->n_ib, 256)), dim3(256), 0, s, g->ib,
                          g->n_ib, g->nbase, g->ncoef32, g->ms, d * bn, g->ibs,
@@ -1360,7 +1502,7 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
     PC_HIP_CHECK(hipGetLastError());
   }
   PC_HIP_CHECK(hipStreamSynchronize(s));
-  g->bytes = geom_bytes_for(d, G, M, k_grid, bn, g->n_ib, g->n_near, g->near_w, want64, want32,
+  g->bytes = geom_bytes_for(d, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near, g->near_w, want64, want32,
                             k_self, g->n_v);
   return PC_OK;
 }
@@ -1461,7 +1603,9 @@ int pc_geom_export(const pc_geom* g, int32_t* gidx, double* gcoef, int32_t* nbas
                        nbase);
     PC_HIP_CHECK(hipGetLastError());
   }
-  if (ncoef && g->M)
+  if (ncoef && g->fit)
+    PC_TRY(launch_fit_export(g, nullptr, g->M, ncoef, g->M, nullptr, s));
+  else if (ncoef && g->M)
     PC_HIP_CHECK(hipMemcpy2DAsync(ncoef, (size_t)g->M * 8, g->ncoef, (size_t)g->ms * 8,
                                   (size_t)g->M * 8, (size_t)g->d * g->bn,
                                   hipMemcpyDeviceToDevice, s));
@@ -1491,7 +1635,7 @@ int pc_geom_footprint(const pc_plan* P, int64_t M, int64_t n_ib, int64_t n_near,
   // the near table is as wide as the most B+V entries of a near point: at
   // most k_grid, rounded up to the kernel's widths
   const int near_w = k_grid <= 8 ? 8 : (k_grid <= 16 ? 16 : (k_grid <= 27 && d == 3 ? 27 : 32));
-  const int64_t gb = geom_bytes_for(d, P->G, M, k_grid, bn, n_ib, n_near, near_w, want64, want32,
+  const int64_t gb = geom_bytes_for(d, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64, want32,
                                     k_self, n_ib) + (cell ? M * 4 : 0);
   if (geom_bytes) *geom_bytes = gb;
   if (build_peak_bytes) *build_peak_bytes = gb + build_scratch_bytes(d, P->G, M, cell);
@@ -1555,6 +1699,8 @@ int pc_geom_export_at(const pc_geom* g, const int64_t* grid_pts, int64_t n_grid,
                      g->k_grid, g->d, grid_pts, n_grid, grid_idx, grid_coef, g->nbase, g->ncoef,
                      g->M, g->ms, g->bn, nodes, n_nodes, node_base, node_coef, bad);
   PC_HIP_CHECK(hipGetLastError());
+  if (node_coef && g->fit)
+    PC_TRY(launch_fit_export(g, nodes, n_nodes, node_coef, n_nodes, bad, s));
   int32_t hbad = 0;
   PC_HIP_CHECK(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
   PC_HIP_CHECK(hipStreamSynchronize(s));
