@@ -124,12 +124,15 @@ typedef struct pc_wls_opts {
                      /* the geometric mean of the per-axis spacings)        */
   int32_t dtype_mask;/* stencil precisions to keep: bit (1 << PC_F64)       */
                      /* float64 (PC_F64 and PC_MIXED), bit (1 << PC_F32)    */
-                     /* float32 (PC_F32); 0 = float64 only.  A float32-only */
-                     /* geometry (1 << PC_F32) holds half the coefficient   */
-                     /* bytes (the 512^3 case of Sec. 3 fits only so in     */
-                     /* float32) and refuses float64 calls and coefficient  */
-                     /* exports with PC_ERR_INVALID_ARG; other bits: the    */
-                     /* same error                                          */
+                     /* float32 (PC_F32); 0 = float64 only.  Most            */
+                     /* coefficients are evaluated in float64 from rows     */
+                     /* that every geometry keeps; the mask governs those   */
+                     /* stored per precision (the near-IB table, node       */
+                     /* stencils smaller than their block, clouds much      */
+                     /* finer than the grid, node-to-node stencils).  A     */
+                     /* float32-only geometry (1 << PC_F32) refuses float64 */
+                     /* calls and coefficient exports with                  */
+                     /* PC_ERR_INVALID_ARG; other bits: the same error      */
   int32_t k_self;    /* > 0: also build node-to-node stencils of k_self     */
                      /* other nodes for the first fractional step           */
                      /* (pc_momentum_predict); 0 = none                    */

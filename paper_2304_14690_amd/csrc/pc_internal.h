@@ -97,11 +97,18 @@ struct pc_geom {
   int device;
   bool has32;   // float32 stencil copies (PC_F32)
   bool has64;   // float64 stencils (PC_F64, PC_MIXED); a float32-only
-                // geometry keeps null float64 coefficient arrays
-  // grid-target stencils
-  int32_t* gidx;   // [k_grid][G]
-  double* gcoef;   // [d][k_grid][G] or null (float32 only)
-  float* gcoef32;  // [d][k_grid][G] or null
+                // geometry keeps null float64 arrays of stored coefficients
+  // grid-target stencils: the nodes, and the quadratics their coefficients are
+  // evaluated from (pc_stencil.h; float64 for every precision) or, for clouds
+  // much finer than the grid (gfit false), the coefficients
+  bool gfit;
+  int32_t* gblk;   // [ntile][k_grid * TP]
+  int32_t* gcnt;   // [ntile]
+  int gmax;        // most nodes of a tile's list
+  double* grow;    // [ntile][grid_rows(d)][TP] or null
+  double* gcoef;   // [ntile][d * k_grid][TP] or null
+  float* gcoef32;  // or null
+  double* xyz;     // [d][ms] node positions
   // node stencils (block order)
   int32_t* nbase;   // [M] flat index of the block's low corner; ~corner
                     // (negative) for a block that wraps around a periodic axis
@@ -109,10 +116,9 @@ struct pc_geom {
                     // to 64, so that every stream starts on a 512-byte line
   // fit = m_node where a node's rows are evaluated from its position
   // (pc_stencil.h: k_node fills the block of 3 or 4 lines per axis): no node
-  // coefficients are kept, xyz holds the node positions.  0: stored rows.
+  // coefficients are kept.  0: stored rows.
   int fit;
   double hsup, eps; // support radius, Eq. 17's shape parameter
-  double* xyz;      // [d][ms] or null
   double* ncoef;    // [d][bn][ms] or null
   float* ncoef32;   // [d][bn][ms] or null
   // IB lists

@@ -274,4 +274,249 @@ __device__ __forceinline__ void block_coef(const NodeFit& A, const BlockFit<D, M
   block_grad<D, MB>(A, B, rd, c);
 }
 
+// ---- grid targets ---------------------------------------------------------------
+// A grid point's nodes lie scattered, but its coefficients are the weight
+// times a quadratic in the node's offset t (Eq. 13: c_a = w q . (C^-1)_a):
+//   c_a(t) = exp(-alpha |t|^2) (l0 + t . l + t . Q t)_a
+// so a geometry keeps the d quadratics and alpha (the rows of C^-1 with the
+// powers of 1/h_t folded in; their linear parts are symmetric in (a, b)) and
+// the transfers evaluate the coefficients from the node positions: 12 (2D) or
+// 28 (3D) float64 per grid point instead of 32 or 81 per precision.
+constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
+
+// The grid points are stored by tiles of tile_x * tile_y * tile_z points (one
+// workgroup each).  The stencils of a tile share most of their nodes (1.7
+// distinct ones per point in 2D and 2.9 in 3D against 16 and 27 entries), so
+// a tile keeps the ascending list of its nodes and each stencil entry is a
+// 16-bit place in that list: a workgroup gathers every node once into LDS and
+// the entries are read from there (a place is the byte offset of its first
+// pair there).  A tile's block of 4 k TP bytes holds the places, two to a
+// word, [ceil(k/2)][TP], then the list; where a tile has
+// more nodes than tile_cap (a cloud much finer than the grid) its count is -1
+// and the block holds the node indices themselves, [k][TP].
+constexpr int tile_x(int d) { return d == 2 ? 32 : 16; }
+constexpr int tile_y(int d) { return d == 2 ? 8 : 4; }
+constexpr int tile_z(int d) { return d == 2 ? 1 : 4; }
+constexpr int tile_points(int d) { return tile_x(d) * tile_y(d) * tile_z(d); }
+// Words of places in a tile's block.
+constexpr int64_t tile_words(int d, int k) { return (int64_t)(k + 1) / 2 * tile_points(d); }
+// LDS bytes from one node to the next: pairs (x, y), (v_x, v_y) in two planes
+// in 2D; (x, y), (z, v_x), (v_y, v_z) next to each other in 3D, where the
+// stride of 12 words keeps the lanes of a b128 read in different banks.
+constexpr int tile_stride(int d) { return d == 2 ? 16 : 48; }
+// Nodes a tile's LDS copy may hold: places are 16 bits, and the list has to
+// fit the block.
+constexpr int tile_cap(int d, int k) {
+  const int64_t room = (int64_t)k * tile_points(d) - tile_words(d, k);
+  const int64_t cap = d == 2 ? 2048 : 65536 / tile_stride(3);
+  return (int)(cap < room ? cap : room);
+}
+
+struct GridFit {
+  int32_t n[3], nt[3];     // grid points and tiles per axis
+  int32_t k;
+  int32_t direct;          // no tile lists (eps beyond row_weight's range)
+  double off, h[3];
+  double L[3], iL[3];      // box length and its inverse on periodic axes, else 0
+  int64_t ms;
+  const int32_t* blk;      // [ntile][k * TP] words
+  const int32_t* cnt;      // [ntile] nodes of the tile's list, or -1
+  const double* rows;      // [ntile][grid_rows(d)][TP], or null: stored coefficients
+  const double* c64;       // [ntile][d * k][TP] (component a, entry i at a * k + i)
+  const float* c32;        // or null
+  const double* x;         // [d][ms] node positions
+};
+
+// Whether a geometry keeps rows.  A cloud much finer than the grid shares few
+// nodes between grid points: its tiles outgrow their LDS lists from about 6 G
+// (2D) or 2.4 G (3D) nodes on, and gathering position and value of every
+// entry from memory costs more than streaming stored coefficients (96^3 grid,
+// 8 nodes a cell: 593 against 218 us in float64, 487 against 149 in float32),
+// so such clouds keep those.
+inline bool grid_rows_kept(int d, int64_t G, int64_t M) { return M <= (d == 2 ? 5 : 2) * G; }
+
+GridFit grid_fit_args(const pc_geom* g);
+inline int64_t grid_tiles(int d, const int32_t* n) {
+  return (int64_t)((n[0] + tile_x(d) - 1) / tile_x(d)) * ((n[1] + tile_y(d) - 1) / tile_y(d)) *
+         (d == 3 ? (n[2] + tile_z(d) - 1) / tile_z(d) : 1);
+}
+
+// A grid point by tile and place in the tile.
+template <int D>
+struct TilePoint {
+  int64_t tile;
+  int t;
+  int c[3];  // grid lines
+
+  __device__ __forceinline__ bool inside(const GridFit& A) const {
+    return c[0] < A.n[0] && c[1] < A.n[1] && (D == 2 || c[2] < A.n[2]);
+  }
+  __device__ __forceinline__ int64_t flat(const GridFit& A) const {
+    return ((int64_t)c[2] * A.n[1] + c[1]) * A.n[0] + c[0];
+  }
+  __device__ __forceinline__ void position(const GridFit& A, double (&xt)[D]) const {
+#pragma unroll
+    for (int a = 0; a < D; ++a) xt[a] = ((double)c[a] + A.off) * A.h[a];
+  }
+};
+
+template <int D>
+__device__ __forceinline__ TilePoint<D> tile_point(const GridFit& A, int64_t tile, int t) {
+  TilePoint<D> P;
+  P.tile = tile;
+  P.t = t;
+  const uint32_t r = (uint32_t)tile / (uint32_t)A.nt[0];  // tiles are counted in 31 bits
+  const int tx = (int)((uint32_t)tile - r * (uint32_t)A.nt[0]);
+  const int tz = D == 3 ? (int)(r / (uint32_t)A.nt[1]) : 0;
+  const int ty = (int)r - tz * A.nt[1];
+  constexpr int X = tile_x(D), Y = tile_y(D);
+  P.c[0] = tx * X + t % X;
+  P.c[1] = ty * Y + (t / X) % Y;
+  P.c[2] = D == 3 ? tz * tile_z(D) + t / (X * Y) : 0;
+  return P;
+}
+
+// The same for flat grid index p.
+template <int D>
+__device__ __forceinline__ TilePoint<D> tile_point_of(const GridFit& A, int64_t p) {
+  TilePoint<D> P;
+  const int64_t r = p / A.n[0];
+  P.c[0] = (int)(p - r * A.n[0]);
+  P.c[2] = D == 3 ? (int)(r / A.n[1]) : 0;
+  P.c[1] = (int)(r - (int64_t)P.c[2] * A.n[1]);
+  constexpr int X = tile_x(D), Y = tile_y(D), Z = tile_z(D);
+  P.tile = ((int64_t)(P.c[2] / Z) * A.nt[1] + P.c[1] / Y) * A.nt[0] + P.c[0] / X;
+  P.t = ((P.c[2] % Z) * Y + P.c[1] % Y) * X + P.c[0] % X;
+  return P;
+}
+
+// Node of entry i of a grid point's stencil.
+template <int D>
+__device__ __forceinline__ int32_t grid_node(const GridFit& A, const TilePoint<D>& P, int i) {
+  constexpr int TP = tile_points(D);
+  const int32_t* b = A.blk + P.tile * ((int64_t)A.k * TP);
+  if (A.cnt[P.tile] < 0) return b[(int64_t)i * TP + P.t];
+  const uint32_t w = (uint32_t)b[(int64_t)(i >> 1) * TP + P.t];
+  return b[tile_words(D, A.k) + ((i & 1) ? w >> 16 : w & 0xffffu) / tile_stride(D)];
+}
+
+// Row r: constants [D], linear parts (a <= b) [D (D + 1) / 2], squares and
+// products (a <= b) [D (D + 1) / 2] per component, -alpha log2(e).
+template <int D>
+struct GridRows {
+  double r[grid_rows(D)];
+};
+
+template <int D>
+__device__ __forceinline__ GridRows<D> load_rows(const GridFit& A, const TilePoint<D>& P) {
+  constexpr int TP = tile_points(D), NR = grid_rows(D);
+  const double* b = A.rows + P.tile * ((int64_t)NR * TP) + P.t;
+  GridRows<D> R;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) R.r[i] = __builtin_nontemporal_load(b + i * TP);
+  return R;
+}
+
+__host__ __device__ constexpr int sym(int d, int a, int b) {
+  return a > b ? sym(d, b, a) : (d == 2 ? a + b : (a == 0 ? b : a + b + 1));
+}
+
+template <int D, int A>
+__device__ __forceinline__ double row_poly_one(const GridRows<D>& R, const double (&t)[D]) {
+  constexpr int S = D * (D + 1) / 2, Q = D + S + S * A;
+  constexpr int LX = D + sym(D, A, 0), LY = D + sym(D, A, 1), LZ = D + sym(D, A, D - 1);
+  double p = R.r[A];
+  if constexpr (D == 2) {
+    double f = __builtin_fma(t[0], R.r[Q], R.r[LX]);
+    p = __builtin_fma(t[0], __builtin_fma(t[1], R.r[Q + 1], f), p);
+    p = __builtin_fma(t[1], __builtin_fma(t[1], R.r[Q + 2], R.r[LY]), p);
+  } else {
+    double f = __builtin_fma(t[0], R.r[Q], R.r[LX]);
+    f = __builtin_fma(t[1], R.r[Q + 1], f);
+    p = __builtin_fma(t[0], __builtin_fma(t[2], R.r[Q + 2], f), p);
+    f = __builtin_fma(t[1], R.r[Q + 3], R.r[LY]);
+    p = __builtin_fma(t[1], __builtin_fma(t[2], R.r[Q + 4], f), p);
+    p = __builtin_fma(t[2], __builtin_fma(t[2], R.r[Q + 5], R.r[LZ]), p);
+  }
+  return p;
+}
+
+template <int D>
+__device__ __forceinline__ void row_poly(const GridRows<D>& R, const double (&t)[D],
+                                         double (&P)[D]) {
+  P[0] = row_poly_one<D, 0>(R, t);
+  P[1] = row_poly_one<D, 1>(R, t);
+  if constexpr (D == 3) P[2] = row_poly_one<D, 2>(R, t);
+}
+
+// Offset of a node at x from a grid point, the nearest image on periodic axes.
+template <int D, bool PER>
+__device__ __forceinline__ void grid_offset(const GridFit& A, const double (&x)[D],
+                                            const double (&xt)[D], double (&t)[D]) {
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    t[a] = x[a] - xt[a];
+    if (PER) t[a] = __builtin_fma(-A.L[a], __builtin_rint(t[a] * A.iL[a]), t[a]);
+  }
+}
+
+// exp(-alpha |t|^2) as 2^y, y = -alpha log2(e) |t|^2 = k + f, |f| <= 1/2: the
+// product is never rounded on its own (both uses are fused), and the degree-11
+// polynomial (the minimax fit of (2^f - 1 - f ln 2) / f^2) leaves 1e-17.
+// Without CLAMP y must stay above -1022 (alpha |t|^2 <= eps: GridFit.direct).
+template <int D, bool CLAMP>
+__device__ __forceinline__ double row_weight(const GridRows<D>& R, const double (&t)[D]) {
+  constexpr double MAGIC = 6755399441055744.0;  // 1.5 2^52
+  const double na = R.r[grid_rows(D) - 1];
+  double r2 = t[0] * t[0];
+#pragma unroll
+  for (int a = 1; a < D; ++a) r2 = __builtin_fma(t[a], t[a], r2);
+  const double m = __builtin_fma(na, r2, MAGIC);
+  const double f = __builtin_fma(na, r2, MAGIC - m);
+  double p = 4.4541068401718916193e-10;
+  p = __builtin_fma(p, f, 7.0709843005464476907e-9);
+  p = __builtin_fma(p, f, 1.0178067252442298443e-7);
+  p = __builtin_fma(p, f, 1.3215451605067549985e-6);
+  p = __builtin_fma(p, f, 0.000015252733820815905329);
+  p = __builtin_fma(p, f, 0.00015403530424814240039);
+  p = __builtin_fma(p, f, 0.0013333558146423204744);
+  p = __builtin_fma(p, f, 0.0096181291076186498546);
+  p = __builtin_fma(p, f, 0.055504108664821582574);
+  p = __builtin_fma(p, f, 0.24022650695910076149);
+  p = __builtin_fma(p, f, 6.9314718055994530942e-1);
+  p = __builtin_fma(p, f, 1.0);
+  // the low word of m is k
+  int k = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
+  if (CLAMP) k = max(k, -1000);
+  const uint64_t pb = __builtin_bit_cast(uint64_t, p);
+  const uint32_t hi = (uint32_t)(pb >> 32) + ((uint32_t)k << 20);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)pb);
+}
+
+// The coefficients of entry i (node j) of a grid point at xt: from its rows,
+// or the stored ones.
+template <int D>
+__device__ __forceinline__ void grid_coef(const GridFit& A, const TilePoint<D>& P,
+                                          const double (&xt)[D], int i, int64_t j,
+                                          double (&c)[D]) {
+  if (!A.rows) {
+    constexpr int TP = tile_points(D);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const int64_t at = (P.tile * (D * A.k) + a * A.k + i) * TP + P.t;
+      c[a] = A.c64 ? A.c64[at] : (double)A.c32[at];
+    }
+    return;
+  }
+  const GridRows<D> R = load_rows<D>(A, P);
+  double x[D], t[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) x[a] = A.x[a * A.ms + j];
+  grid_offset<D, true>(A, x, xt, t);
+  row_poly<D>(R, t, c);
+  const double w = row_weight<D, true>(R, t);
+#pragma unroll
+  for (int a = 0; a < D; ++a) c[a] *= w;
+}
+
 }  // namespace pc

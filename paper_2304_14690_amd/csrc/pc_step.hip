@@ -6,18 +6,19 @@
 //   ib_update     g = -u* + G at the B+V nodes, criterion sums      (Eq. 19)
 //   project       u^{n+1} = u* - G on F, exactly 0 on B+V          (Eq. 18)
 //
-// The gathers are one thread per target.  Stencil arrays are laid out
-// [entry][target] so that a wavefront reads 64 consecutive targets of one
-// entry in one coalesced access; they are streamed with non-temporal loads so
-// that the gathered field values (re-read by neighbouring targets) keep the
-// caches.  In float32 mode the sums are taken relative to the value at the
-// first stencil entry: the derivative rows annihilate constants, and the
-// differences avoid the cancellation of sum_i c_i v_i (|c| ~ 1/h) in float32.
+// The gathers are one thread per target; per-target arrays are laid out so
+// that a wavefront reads 64 targets in one coalesced access, streamed with
+// non-temporal loads.  Most coefficients are evaluated where they are applied
+// (pc_stencil.h), in float64 in every precision.  Where stored float32
+// coefficients are read, the sums are taken relative to the value at the first
+// stencil entry: the derivative rows annihilate constants, and the differences
+// avoid the cancellation of sum_i c_i v_i (|c| ~ 1/h) in float32.
 #include <cmath>
 #include <cstring>
 
 #include <chrono>
 #include <mutex>
+#include <type_traits>
 
 #include "pc_internal.h"
 #include "pc_stencil.h"
@@ -44,13 +45,43 @@ NodeFit node_fit_args(const pc_geom* g) {
   return A;
 }
 
+GridFit grid_fit_args(const pc_geom* g) {
+  GridFit A;
+  std::memset(&A, 0, sizeof(A));
+  const int d = g->d;
+  A.off = g->vertex ? 0.0 : 0.5;
+  A.k = g->k_grid;
+  A.direct = g->eps > 690.0;
+  A.ms = g->ms;
+  A.blk = g->gblk;
+  A.cnt = g->gcnt;
+  A.rows = g->grow;
+  A.c64 = g->gcoef;
+  A.c32 = g->gcoef32;
+  A.x = g->xyz;
+  const int T[3] = {tile_x(d), tile_y(d), tile_z(d)};
+  for (int a = 0; a < 3; ++a) {
+    A.n[a] = a < d ? g->n[a] : 1;
+    A.nt[a] = (A.n[a] + T[a] - 1) / T[a];
+    A.h[a] = g->h[a];
+    if (a < d && ((g->per >> a) & 1)) {
+      A.L[a] = (double)g->n[a] * g->h[a];
+      A.iL[a] = 1.0 / A.L[a];
+    }
+  }
+  return A;
+}
+
 namespace {
 
 constexpr int XCDS = 8;
 
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
-  if (nb % XCDS != 0) return b;
-  return (b % XCDS) * (nb / XCDS) + b / XCDS;
+// Workgroups go to the XCDs in turn; work item xcd_block(b, nb) of workgroup b
+// gives every XCD a contiguous part of nb items (the first nb % 8 XCDs one
+// more).
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb) {
+  const uint32_t x = b % XCDS;
+  return x * (nb / XCDS) + min(x, nb % XCDS) + b / XCDS;
 }
 
 template <typename T>
@@ -62,63 +93,134 @@ constexpr int TPB = 256;
 constexpr int IBT = 64;  // threads per block of the IB iteration kernel (one wavefront)
 
 // ---- div_to_grid (all grid points) -------------------------------------------
-// Order of the grid points over the workgroups of a 3D launch.  A workgroup
-// takes TPB consecutive points of one x row (coalesced stencil streams);
-// with `on`, the workgroups that one XCD runs in a row cover blocks of
-// SY rows x SZ planes (all of each row), swept along y within slabs of SZ
-// planes, so that the node values gathered for a block (the stencils reach
-// one or two lines beyond it in every direction) are fetched into that
-// XCD's L2 about once instead of once per plane that needs them.
-struct DivMap {
-  int on;
-  int segs;       // TPB-point segments per row (n0 / TPB)
-  int tiles_y;    // n1 / SY
-  int64_t n0, n1;
-};
-constexpr int DIV_SY = 8, DIV_SZ = 16;
-
-__device__ __forceinline__ int64_t div_point(int64_t blk, const DivMap& m) {
-  if (!m.on) return blk * TPB + threadIdx.x;
-  const int64_t per = (int64_t)m.segs * DIV_SY * DIV_SZ;
-  const int64_t st = blk / per;
-  const int64_t r = blk - st * per;
-  const int64_t seg = r % m.segs;
-  const int64_t zz = (r / m.segs) % DIV_SZ;
-  const int64_t yy = r / ((int64_t)m.segs * DIV_SZ);
-  const int64_t ty = st % m.tiles_y, tz = st / m.tiles_y;
-  const int64_t y = ty * DIV_SY + yy, z = tz * DIV_SZ + zz;
-  return (z * m.n1 + y) * m.n0 + seg * TPB + threadIdx.x;
-}
-
-template <typename T, int D, int K, bool LOCALREF>
-__global__ void __launch_bounds__(TPB) k_div_all(const int32_t* __restrict__ gidx,
-                                                 const T* __restrict__ gcoef, int64_t G, int krt,
-                                                 const T* __restrict__ v, int64_t M,
-                                                 T* __restrict__ b, DivMap dm) {
-  const int k = K > 0 ? K : krt;
-  const int64_t p = div_point(xcd_block(blockIdx.x, gridDim.x), dm);
-  if (p >= G) return;
-  T acc = T(0);
-  T ref[D];
+// Stored coefficients (clouds much finer than the grid, GridFit.rows null).
+template <typename T, int D, int K>
+__global__ void __launch_bounds__(tile_points(D)) k_div_stored(GridFit A,
+                                                               const T* __restrict__ coef,
+                                                               const T* __restrict__ v, int64_t M,
+                                                               T* __restrict__ b) {
+  constexpr int TP = tile_points(D);
+  constexpr bool LOCALREF = sizeof(T) == 4;
+  const int k = K > 0 ? K : A.k;
+  const TilePoint<D> P = tile_point<D>(A, xcd_block(blockIdx.x, gridDim.x), threadIdx.x);
+  if (!P.inside(A)) return;
+  const int32_t* const idx = A.blk + P.tile * ((int64_t)k * TP) + P.t;
+  const T* const c = coef + P.tile * ((int64_t)D * k * TP) + P.t;
+  T acc = T(0), ref[D];
   if (LOCALREF) {
-    int j0 = ldnt(gidx + p);
+    const int64_t j0 = ldnt(idx);
 #pragma unroll
     for (int a = 0; a < D; ++a) ref[a] = v[a * M + j0];
   }
-  // four entries at a time (a full unroll of the 27 entries, every index
-  // load issued up front, was 2.6% slower at 512^3)
 #pragma unroll 4
   for (int i = 0; i < k; ++i) {
-    int j = ldnt(gidx + (int64_t)i * G + p);
+    const int64_t j = ldnt(idx + i * TP);
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      T c = ldnt(gcoef + ((int64_t)a * k + i) * G + p);
       T val = v[a * M + j];
       if (LOCALREF) val -= ref[a];
-      acc += c * val;
+      acc += ldnt(c + (a * k + i) * TP) * val;
     }
   }
-  b[p] = acc;
+  b[P.flat(A)] = acc;
+}
+
+// Coefficients from rows.  The 27-point float64 divergence streamed 788 bytes
+// a point from stored coefficients; from rows it moves about 370 (224 of
+// rows, 56 of places, the list, positions and values of the tile's nodes) and
+// issues 51 float64 operations an entry, so that HBM (4.8 TB/s) and the
+// vector units (80% busy at the clock the chip then holds, 1.7-2.1 GHz) bound
+// it together: 512 x 256 x 256 5.86 -> 2.63 ms, 128^3 356 -> 160 us, 2048^2
+// (k = 16, 184 bytes a point, 5.6 TB/s) 288 -> 137 us; float32 (the same
+// float64 coefficients) 200 x 168 x 120 386 -> 361 us, 2048^2 164 -> 121 us.
+// Gathering each entry's six values from memory instead of LDS costs 41
+// cycles a load and wave, 5.7 ms at 512 x 256 x 256.  Tiles of 16 x 8 x 4 and
+// 8 x 8 x 8 points (512 threads, two workgroups a compute unit instead of
+// four) take 2.78 and 2.73 ms against 2.63, 8 x 4 x 4 2.87; sweeping the tiles
+// in slabs along y, so that an XCD's L2 holds the planes tiles share, changes
+// nothing (2.72-2.78).
+template <typename T, int D, int K, bool PER>
+__global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* __restrict__ v,
+                                                            int64_t M, T* __restrict__ b, int cap) {
+  constexpr int TP = tile_points(D);
+  extern __shared__ __attribute__((aligned(16))) char node[];
+  // bytes between the pairs of a node
+  const int pair = D == 2 ? cap * 16 : 16;
+  const int k = K > 0 ? K : A.k;
+  const TilePoint<D> P = tile_point<D>(A, xcd_block(blockIdx.x, gridDim.x), threadIdx.x);
+  const int n = A.cnt[P.tile];
+  const int32_t* const blk = A.blk + P.tile * ((int64_t)k * TP);
+  // the point's own streams first: they are in flight while the nodes are
+  // gathered
+  const GridRows<D> R = load_rows<D>(A, P);
+  constexpr int KW = K > 0 ? (K + 1) / 2 : 1;
+  uint32_t w[KW];
+  if (K > 0) {
+#pragma unroll
+    for (int i = 0; i < KW; ++i) w[i] = (uint32_t)ldnt(blk + i * TP + P.t);
+  }
+  // positions and values of the tile's nodes into LDS
+  for (int s = threadIdx.x; s < n; s += TP) {
+    const int64_t j = blk[tile_words(D, k) + s];
+    double f[2 * D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      f[a] = A.x[a * A.ms + j];
+      f[D + a] = (double)v[a * M + j];
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+      *reinterpret_cast<double2*>(node + s * tile_stride(D) + a * pair) =
+          double2{f[2 * a], f[2 * a + 1]};
+  }
+  double xt[D], acc = 0.0;
+  P.position(A, xt);
+  auto entry = [&](const double (&f)[2 * D], auto clamp) {
+    double x[D], t[D], c[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) x[a] = f[a];
+    grid_offset<D, PER>(A, x, xt, t);
+    row_poly<D>(R, t, c);
+    double s = c[0] * f[D];
+#pragma unroll
+    for (int a = 1; a < D; ++a) s = __builtin_fma(c[a], f[D + a], s);
+    acc = __builtin_fma(row_weight<D, decltype(clamp)::value>(R, t), s, acc);
+  };
+  __syncthreads();
+  if (!P.inside(A)) return;
+  if (n >= 0) {
+    auto place = [&](uint32_t l) {
+      double f[2 * D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const double2 q = *reinterpret_cast<const double2*>(node + l + a * pair);
+        f[2 * a] = q.x;
+        f[2 * a + 1] = q.y;
+      }
+      entry(f, std::false_type{});
+    };
+    if constexpr (K > 0) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) place((i & 1) ? w[i / 2] >> 16 : w[i / 2] & 0xffffu);
+    } else {
+      for (int i = 0; i < k; ++i) {
+        const uint32_t wi = (uint32_t)ldnt(blk + (i / 2) * TP + P.t);
+        place((i & 1) ? wi >> 16 : wi & 0xffffu);
+      }
+    }
+  } else {
+    for (int i = 0; i < k; ++i) {
+      const int64_t j = ldnt(blk + i * TP + P.t);
+      double f[2 * D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        f[a] = A.x[a * A.ms + j];
+        f[D + a] = (double)v[a * M + j];
+      }
+      entry(f, std::true_type{});
+    }
+  }
+  b[P.flat(A)] = (T)acc;
 }
 
 // ---- criterion of the IB iteration (Sec. 2.3) ------------------------------------
@@ -353,7 +455,7 @@ __global__ void __launch_bounds__(TPB) k_grad_all(const int32_t* __restrict__ nb
   // block lines per axis (16 = 4^2 in 2D, 27 = 3^3 in 3D)
   constexpr int MB = BN == 16 && D == 2 ? 4 : (BN == 27 && D == 3 ? 3 : 0);
   const int m = MB > 0 ? MB : bo.m;
-  const int64_t n = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
+  const int64_t n = (int64_t)xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
   if (n >= M) return;
   const int32_t b32 = ldnt(nbase + n);
   const int64_t base = WRAP ? (b32 >= 0 ? b32 : ~b32) : b32;
@@ -425,7 +527,7 @@ __global__ void __launch_bounds__(TPB) k_grad_fit(const int32_t* __restrict__ nb
                                                   T* __restrict__ out,
                                                   const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
-  const int64_t n = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
+  const int64_t n = (int64_t)xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
   if (n >= M) return;
   const int32_t b32 = ldnt(nbase + n);
   double x[D], G[D];
@@ -795,33 +897,31 @@ int check_dtype(const pc_geom* g, int dtype) {
 }
 
 // ---- launch helpers ---------------------------------------------------------------
-// The block order of k_div_all (see DivMap): on 3D grids whose rows split
-// into whole workgroups and whose y and z extents hold whole blocks.
-DivMap div_map(const pc_geom* g) {
-  DivMap m{};
-  if (g->d == 3 && g->n[0] % TPB == 0 && g->n[1] % DIV_SY == 0 && g->n[2] % DIV_SZ == 0) {
-    m.on = 1;
-    m.segs = g->n[0] / TPB;
-    m.tiles_y = g->n[1] / DIV_SY;
-    m.n0 = g->n[0];
-    m.n1 = g->n[1];
-  }
-  return m;
-}
-
 template <typename T>
-int launch_div_all(const pc_geom* g, const T* gcoef, const T* v, T* b, hipStream_t s) {
-  const bool lr = sizeof(T) == 4;
-  dim3 grid(nblk(g->G)), block(TPB);
-  const DivMap dm = div_map(g);
-#define DIVL(D, K)                                                                           \
-  do {                                                                                      \
-    if (lr)                                                                                 \
-      hipLaunchKernelGGL((k_div_all<T, D, K, true>), grid, block, 0, s, g->gidx, gcoef, g->G, \
-                         g->k_grid, v, g->M, b, dm);                                       \
-    else                                                                                    \
-      hipLaunchKernelGGL((k_div_all<T, D, K, false>), grid, block, 0, s, g->gidx, gcoef, g->G, \
-                         g->k_grid, v, g->M, b, dm);                                       \
+int launch_div_all(const pc_geom* g, const T* v, T* b, hipStream_t s) {
+  const GridFit gf = grid_fit_args(g);
+  const dim3 grid((unsigned)((int64_t)gf.nt[0] * gf.nt[1] * gf.nt[2])), block(tile_points(g->d));
+  if (!g->gfit) {
+    const T* coef = sizeof(T) == 8 ? (const T*)g->gcoef : (const T*)g->gcoef32;
+#define DIVS(D, K) hipLaunchKernelGGL((k_div_stored<T, D, K>), grid, block, 0, s, gf, coef, v, g->M, b)
+    if (g->d == 2) {
+      if (g->k_grid == 16) DIVS(2, 16); else DIVS(2, 0);
+    } else {
+      if (g->k_grid == 27) DIVS(3, 27); else DIVS(3, 0);
+    }
+#undef DIVS
+    PC_HIP_CHECK(hipGetLastError());
+    return PC_OK;
+  }
+  const size_t lds = (size_t)g->gmax * g->d * 16;
+#define DIVL(D, K)                                                                             \
+  do {                                                                                         \
+    if (g->per)                                                                                \
+      hipLaunchKernelGGL((k_div_all<T, D, K, true>), grid, block, lds, s, gf, v, g->M, b,       \
+                         g->gmax);                                                             \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_div_all<T, D, K, false>), grid, block, lds, s, gf, v, g->M, b,      \
+                         g->gmax);                                                             \
   } while (0)
   if (g->d == 2) {
     if (g->k_grid == 16) DIVL(2, 16);
@@ -1042,10 +1142,6 @@ int launch_zero_ib(const pc_geom* g, T* out, hipStream_t s, const int32_t* skip 
 }
 
 template <typename T>
-const T* gc(const pc_geom* g) {
-  if constexpr (sizeof(T) == 8) return g->gcoef; else return g->gcoef32;
-}
-template <typename T>
 const T* nc(const pc_geom* g) {
   if constexpr (sizeof(T) == 8) return g->ncoef; else return g->ncoef32;
 }
@@ -1106,7 +1202,7 @@ int pressure_correct_t(const pc_geom* g, const pc_plan* P, int mode, const T* u,
   const int64_t nib = g->n_ib;
 
   // the long gather goes first so that the host queues the rest behind it
-  PC_TRY(launch_div_all<T>(g, gc<T>(g), u, b, s));
+  PC_TRY(launch_div_all<T>(g, u, b, s));
   {
     const unsigned nbib = std::max<unsigned>(1, nblk(nib));
     hipLaunchKernelGGL(k_prologue<T>, dim3(nbib + nblk(g->n_near)), dim3(TPB), 0, s, g->ib, nib,
@@ -1306,7 +1402,7 @@ __global__ void __launch_bounds__(TPB) k_momentum(const int32_t* __restrict__ si
                                                   Force3 F, T* __restrict__ rout,
                                                   T* __restrict__ ustar) {
   const int k = K > 0 ? K : krt;
-  const int64_t n = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
+  const int64_t n = (int64_t)xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
   if (n >= M) return;
   T un[D], lp[D], gr[D][D];
 #pragma unroll
@@ -1492,8 +1588,8 @@ int pc_div_to_grid(const pc_geom* g, int dtype, const void* v, void* b, int subs
   PC_TRY(check_fields(v, b));
   hipStream_t s = as_stream(stream);
   if (subset == PC_ALL) {
-    if (dtype == PC_F64) return launch_div_all<double>(g, g->gcoef, (const double*)v, (double*)b, s);
-    return launch_div_all<float>(g, g->gcoef32, (const float*)v, (float*)b, s);
+    if (dtype == PC_F64) return launch_div_all<double>(g, (const double*)v, (double*)b, s);
+    return launch_div_all<float>(g, (const float*)v, (float*)b, s);
   }
   if (subset == PC_NEAR_IB) {
     if (dtype == PC_F64)

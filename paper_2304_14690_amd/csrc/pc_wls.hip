@@ -410,8 +410,10 @@ struct GridStencilArgs {
   RingArgs r;
   int k;
   double eps, hsup;       // hsup = support * delta
-  int32_t* gidx;          // [k][G]
-  double* gcoef;          // [d][k][G]
+  GridFit f;              // tiles of the grid
+  int32_t* gblk;          // node indices [ntile][k][TP] (k_tile_pack follows)
+  double* grow;           // [ntile][grid_rows(D)][TP], or null: coefficients
+  double* gcoef;          // [ntile][D * k][TP]
   float* gcoef32;
   int32_t* bad;           // singular flag
 };
@@ -419,22 +421,16 @@ struct GridStencilArgs {
 // The ring search is written out here rather than through knn_ring: the
 // shared version costs this kernel its second wavefront per SIMD (register
 // spills into accumulation registers), which doubles the build time.
-template <int D>
+template <int D, bool ROWS>
 __global__ void __launch_bounds__(64) k_grid_stencils(GridStencilArgs GA) {
   constexpr int MU = D == 2 ? 6 : 10;
   const RingArgs& A = GA.r;
-  const int64_t p = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (p >= A.g.G) return;
+  constexpr int TP = tile_points(D);
+  const int64_t tid = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const TilePoint<D> tp = tile_point<D>(GA.f, tid / TP, (int)(tid % TP));
+  if (!tp.inside(GA.f)) return;
   const int k = GA.k;
-  int ci[3] = {0, 0, 0};
-  {
-    int64_t r = p;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      ci[a] = (int)(r % A.g.n[a]);
-      r /= A.g.n[a];
-    }
-  }
+  const int ci[3] = {tp.c[0], tp.c[1], tp.c[2]};
   double xt[3];
 #pragma unroll
   for (int a = 0; a < D; ++a) xt[a] = ((double)ci[a] + A.g.off) * A.g.h[a];
@@ -558,7 +554,34 @@ __global__ void __launch_bounds__(64) k_grid_stencils(GridStencilArgs GA) {
   double y[D][MU];
 #pragma unroll
   for (int a = 0; a < D; ++a) chol_unit_solve<MU>(Cm, 1 + a, y[a]);
-  const int64_t G = A.g.G;
+  double* const grow = GA.grow + tp.tile * ((int64_t)grid_rows(D) * TP) + tp.t;
+  int32_t* const gidx = GA.gblk + tp.tile * ((int64_t)k * TP) + tp.t;
+  // the quadratics of pc_stencil.h in unscaled offsets: constants, linear
+  // parts (symmetric), squares (with Eq. 16's 1/2) and products, exponent
+  if (ROWS) {
+    constexpr int S = D * (D + 1) / 2;
+    const double i2 = iht * iht, i3 = i2 * iht;
+    int r = 0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) grow[r++ * TP] = y[a][0] * iht;
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+      for (int b = a; b < D; ++b) grow[r++ * TP] = y[a][1 + b] * i2;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      int q = 1 + D;
+#pragma unroll
+      for (int b = 0; b < D; ++b)
+#pragma unroll
+        for (int c = b; c < D; ++c) {
+          grow[r++ * TP] = (b == c ? 0.5 : 1.0) * y[a][q] * i3;
+          ++q;
+        }
+    }
+    grow[r * TP] = -1.4426950408889634074 * (GA.eps * i2);
+    static_assert(D + S + S * D + 1 == grid_rows(D), "rows per grid point");
+  }
   // Storage order: by the node's offset from the target in whole grid
   // spacings (rounded per axis, each clamped to [-4, 4]), shortest offsets
   // first, ties by the offset's coordinates (z, y, x), then by node index.
@@ -591,21 +614,24 @@ __global__ void __launch_bounds__(64) k_grid_stencils(GridStencilArgs GA) {
 #pragma unroll
       for (int jj = 0; jj < KMAX; ++jj)
         if (jj < k && (okey[jj] < okey[j] || (okey[jj] == okey[j] && li[jj] < nid))) ++pos;
-      double xi[3];
+      gidx[pos * TP] = nid;
+      if (!ROWS) {
+        double xi[3];
 #pragma unroll
-      for (int a = 0; a < D; ++a) xi[a] = axis_diff(A.xyz[a * A.M + nid], xt[a], A.g, a) / ht;
-      double w = exp((-GA.eps * ld[j]) / (ht * ht));
-      double q[MU];
-      basis<D>(xi, q);
-      GA.gidx[(int64_t)pos * G + p] = nid;
+        for (int a = 0; a < D; ++a) xi[a] = axis_diff(A.xyz[a * A.M + nid], xt[a], A.g, a) / ht;
+        double w = exp((-GA.eps * ld[j]) / (ht * ht));
+        double q[MU];
+        basis<D>(xi, q);
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        double t = 0.0;
+        for (int a = 0; a < D; ++a) {
+          double t = 0.0;
 #pragma unroll
-        for (int r = 0; r < MU; ++r) t += y[a][r] * q[r];
-        double cval = w * t * iht;
-        if (GA.gcoef) GA.gcoef[((int64_t)a * k + pos) * G + p] = cval;
-        if (GA.gcoef32) GA.gcoef32[((int64_t)a * k + pos) * G + p] = (float)cval;
+          for (int r = 0; r < MU; ++r) t += y[a][r] * q[r];
+          const double cval = w * t * iht;
+          const int64_t at = (tp.tile * (D * k) + a * k + pos) * TP + tp.t;
+          if (GA.gcoef) GA.gcoef[at] = cval;
+          if (GA.gcoef32) GA.gcoef32[at] = (float)cval;
+        }
       }
     }
   }
@@ -757,15 +783,13 @@ __global__ void __launch_bounds__(64) k_node_stencils(NodeStencilArgs A) {
 }
 
 // Geometries whose node rows are evaluated from positions (pc_stencil.h): the
-// block corners, the positions in a stream-aligned copy, and the singularity
-// test.  In the order of Eq. 16's terms the pivots of the normal matrix are
+// block corners and the singularity test.  In the order of Eq. 16's terms the pivots of the normal matrix are
 // the squared norms of the products p_i p_j p_k (halved for the squares,
 // scaled by (h / h_t)^(2 (i + j + k))).
 template <int D, int MB>
 __global__ void __launch_bounds__(256) k_node_fit(const double* __restrict__ xyz, int64_t M,
                                                   GridDesc g, NodeFit A,
                                                   int32_t* __restrict__ nbase,
-                                                  double* __restrict__ xo, int64_t ms,
                                                   int32_t* __restrict__ bad) {
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (n >= M) return;
@@ -775,7 +799,6 @@ __global__ void __launch_bounds__(256) k_node_fit(const double* __restrict__ xyz
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     x[a] = xyz[a * M + n];
-    xo[a * ms + n] = x[a];
     double lo = floor(x[a] / g.h[a] - (0.5 * MB - 1.0 + g.off));
     if (!((g.per >> a) & 1)) lo = fmin(fmax(lo, 0.0), (double)(g.n[a] - MB));
     const int b = (int)lo, na = g.n[a];
@@ -989,15 +1012,136 @@ __global__ void __launch_bounds__(64) k_self_stencils(SelfStencilArgs SA) {
   }
 }
 
+// ---- tile lists ------------------------------------------------------------------
+// Turns a tile's node indices into its list of distinct nodes (ascending, so
+// that gathering them is close to contiguous) and the entries' places in it
+// (pc_stencil.h), in the same block of memory: every index is in registers
+// before the block is written.  The distinct nodes are collected in a hash
+// table, sorted (bitonic) and looked up by bisection, all in LDS; gmax takes
+// the longest list.
+constexpr int TILE_HASH = 4096, TILE_SORT = 2048;
+
+template <int D>
+__global__ void __launch_bounds__(tile_points(D)) k_tile_pack(GridFit A, int32_t* __restrict__ blk,
+                                                              int32_t* __restrict__ cnt,
+                                                              int32_t* __restrict__ gmax) {
+  constexpr int TP = tile_points(D);
+  __shared__ int32_t hash[TILE_HASH], list[TILE_SORT];
+  __shared__ int32_t nu, nl;
+  const int k = A.k, cap = A.direct ? 0 : tile_cap(D, k);
+  const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
+  int32_t* const b = blk + P.tile * ((int64_t)k * TP);
+  const bool in = P.inside(A);
+  for (int i = threadIdx.x; i < TILE_HASH; i += TP) hash[i] = -1;
+  if (threadIdx.x == 0) nu = nl = 0;
+  __syncthreads();
+  int32_t e[KMAX];
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    e[i] = -1;
+    if (i < k && in) {
+      const int32_t id = e[i] = b[i * TP + P.t];
+      // at most cap + TP + 1 entries are ever inserted, below the table's
+      // size, so that every search meets its entry or a free place
+      if (__hip_atomic_load(&nu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > cap) continue;
+      for (uint32_t h = ((uint32_t)id * 2654435761u) >> 20;; h = (h + 1) % TILE_HASH) {
+        const int32_t old = atomicCAS(&hash[h], -1, id);
+        if (old == -1) atomicAdd(&nu, 1);
+        if (old == -1 || old == id) break;
+      }
+    }
+  }
+  __syncthreads();
+  const int n = nu;
+  if (n > cap) {
+    if (threadIdx.x == 0) cnt[P.tile] = -1;
+    return;
+  }
+  int n2 = 64;
+  while (n2 < n) n2 *= 2;
+  for (int i = threadIdx.x; i < n2; i += TP) list[i] = 0x7fffffff;
+  __syncthreads();
+  for (int i = threadIdx.x; i < TILE_HASH; i += TP)
+    if (hash[i] >= 0) list[atomicAdd(&nl, 1)] = hash[i];
+  __syncthreads();
+  for (int w = 2; w <= n2; w *= 2) {
+    for (int s = w / 2; s > 0; s /= 2) {
+      for (int q = threadIdx.x; q < n2 / 2; q += TP) {
+        const int lo = 2 * q - (q & (s - 1)), hi = lo + s;
+        const int32_t x = list[lo], y = list[hi];
+        if ((x > y) == ((lo & w) == 0)) {
+          list[lo] = y;
+          list[hi] = x;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  uint32_t word = 0;
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    if (i < k) {
+      int lo = 0, hi = n - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (list[mid] < e[i]) lo = mid + 1; else hi = mid;
+      }
+      const uint32_t at = (uint32_t)lo * tile_stride(D);
+      word = (i & 1) ? word | (at << 16) : at;
+      if ((i & 1) || i == k - 1) b[(i >> 1) * TP + P.t] = (int32_t)word;
+    }
+  }
+  int32_t* const out = b + tile_words(D, k);
+  for (int i = threadIdx.x; i < n; i += TP) out[i] = list[i];
+  if (threadIdx.x == 0) {
+    cnt[P.tile] = n;
+    atomicMax(gmax, n);
+  }
+}
+
 // ---- IB lists ------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_near_flags(const int32_t* __restrict__ gidx, int64_t G,
-                                                    int k, const uint8_t* __restrict__ kind,
-                                                    uint8_t* __restrict__ flag) {
-  int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= G) return;
+template <int D>
+__global__ void __launch_bounds__(256) k_near_flags(GridFit A, const uint8_t* __restrict__ kind,
+                                                    int64_t ntile, uint8_t* __restrict__ flag) {
+  constexpr int TP = tile_points(D);
+  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (tid >= ntile * TP) return;
+  const TilePoint<D> P = tile_point<D>(A, tid / TP, (int)(tid % TP));
+  if (!P.inside(A)) return;
   int cnt = 0;
-  for (int i = 0; i < k; ++i) cnt += kind[gidx[(int64_t)i * G + p]] != PC_KIND_F;
-  flag[p] = (uint8_t)(cnt > 255 ? 255 : cnt);
+  for (int i = 0; i < A.k; ++i) cnt += kind[grid_node<D>(A, P, i)] != PC_KIND_F;
+  flag[P.flat(A)] = (uint8_t)(cnt > 255 ? 255 : cnt);
+}
+
+// Stencil node indices in the exported layout: entry i of grid point pts[t]
+// (null: point t) at i * os + t.
+template <int D>
+__global__ void __launch_bounds__(256) k_index_export(GridFit A, int64_t G,
+                                                      const int64_t* __restrict__ pts, int64_t np_,
+                                                      int32_t* __restrict__ out, int64_t os,
+                                                      int32_t* __restrict__ bad) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= np_) return;
+  const int64_t p = pts ? pts[t] : t;
+  if (p < 0 || p >= G) {
+    if (bad) *bad = 1;
+    return;
+  }
+  const TilePoint<D> P = tile_point_of<D>(A, p);
+  for (int i = 0; i < A.k; ++i) out[(int64_t)i * os + t] = grid_node<D>(A, P, i);
+}
+
+int launch_index_export(const pc_geom* g, const int64_t* pts, int64_t np_, int32_t* out,
+                        int64_t os, int32_t* bad, hipStream_t s) {
+  if (np_ == 0) return PC_OK;
+  const GridFit gf = grid_fit_args(g);
+  const dim3 grid((unsigned)((np_ + 255) / 256)), block(256);
+  if (g->d == 2)
+    hipLaunchKernelGGL(k_index_export<2>, grid, block, 0, s, gf, g->G, pts, np_, out, os, bad);
+  else
+    hipLaunchKernelGGL(k_index_export<3>, grid, block, 0, s, gf, g->G, pts, np_, out, os, bad);
+  PC_HIP_CHECK(hipGetLastError());
+  return PC_OK;
 }
 
 __global__ void __launch_bounds__(256) k_slot_map(const int32_t* __restrict__ ib, int64_t nib,
@@ -1006,32 +1150,77 @@ __global__ void __launch_bounds__(256) k_slot_map(const int32_t* __restrict__ ib
   if (s < nib) slot[ib[s]] = (int32_t)s;
 }
 
-template <typename T>
+// The near-IB table in the kept precisions (nc64, nc32 nullable).
+template <int D>
 __global__ void __launch_bounds__(256) k_near_fill(const int32_t* __restrict__ near, int64_t nnear,
-                                                   int64_t nns, int W,
-                                                   const int32_t* __restrict__ gidx,
-                                                   const T* __restrict__ gcoef, int64_t G, int k,
-                                                   int d, const int32_t* __restrict__ slot,
+                                                   int64_t nns, int W, GridFit A,
+                                                   const int32_t* __restrict__ slot,
                                                    int32_t* __restrict__ nslot,
-                                                   T* __restrict__ ncoefib) {
+                                                   double* __restrict__ nc64,
+                                                   float* __restrict__ nc32) {
   int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= nnear) return;
-  int64_t p = near[q];
+  const TilePoint<D> P = tile_point_of<D>(A, near[q]);
+  double xt[D], c[D];
+  P.position(A, xt);
+  auto put = [&](int e, int s) {
+    nslot[(int64_t)e * nns + q] = s;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const int64_t at = ((int64_t)a * W + e) * nns + q;
+      if (nc64) nc64[at] = c[a];
+      if (nc32) nc32[at] = (float)c[a];
+    }
+  };
   int e = 0;
-  for (int i = 0; i < k; ++i) {
-    int nid = gidx[(int64_t)i * G + p];
+  for (int i = 0; i < A.k; ++i) {
+    int nid = grid_node<D>(A, P, i);
     int s = slot[nid];
     if (s >= 0 && e < W) {
-      nslot[(int64_t)e * nns + q] = s;
-      for (int a = 0; a < d; ++a)
-        ncoefib[((int64_t)a * W + e) * nns + q] = gcoef[((int64_t)a * k + i) * G + p];
-      ++e;
+      grid_coef<D>(A, P, xt, i, nid, c);
+      put(e++, s);
     }
   }
-  for (; e < W; ++e) {
-    nslot[(int64_t)e * nns + q] = -1;
-    for (int a = 0; a < d; ++a) ncoefib[((int64_t)a * W + e) * nns + q] = T(0);
+#pragma unroll
+  for (int a = 0; a < D; ++a) c[a] = 0.0;
+  while (e < W) put(e++, -1);
+}
+
+// Coefficients of the grid points pts[t] (null: point t), component a of
+// entry i at (a * k + i) * os + t (for inspection).
+template <int D>
+__global__ void __launch_bounds__(256) k_grid_export(GridFit A, int64_t G,
+                                                     const int64_t* __restrict__ pts, int64_t np_,
+                                                     double* __restrict__ out, int64_t os,
+                                                     int32_t* __restrict__ bad) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= np_) return;
+  const int64_t p = pts ? pts[t] : t;
+  if (p < 0 || p >= G) {
+    if (bad) *bad = 1;
+    return;
   }
+  const TilePoint<D> P = tile_point_of<D>(A, p);
+  double xt[D], c[D];
+  P.position(A, xt);
+  for (int i = 0; i < A.k; ++i) {
+    grid_coef<D>(A, P, xt, i, grid_node<D>(A, P, i), c);
+#pragma unroll
+    for (int a = 0; a < D; ++a) out[((int64_t)a * A.k + i) * os + t] = c[a];
+  }
+}
+
+int launch_grid_export(const pc_geom* g, const int64_t* pts, int64_t np_, double* out, int64_t os,
+                       int32_t* bad, hipStream_t s) {
+  if (np_ == 0) return PC_OK;
+  const GridFit gf = grid_fit_args(g);
+  const dim3 grid((unsigned)((np_ + 255) / 256)), block(256);
+  if (g->d == 2)
+    hipLaunchKernelGGL(k_grid_export<2>, grid, block, 0, s, gf, g->G, pts, np_, out, os, bad);
+  else
+    hipLaunchKernelGGL(k_grid_export<3>, grid, block, 0, s, gf, g->G, pts, np_, out, os, bad);
+  PC_HIP_CHECK(hipGetLastError());
+  return PC_OK;
 }
 
 template <typename T>
@@ -1058,48 +1247,28 @@ __global__ void __launch_bounds__(256) k_base_export(const int32_t* __restrict__
   }
 }
 
-// Stencils of selected targets, for inspection: grid stencils of the grid
-// points pts[t] and node stencils of the nodes nds[t] (one thread per target
-// and array); an index out of range sets *bad and is skipped.
-__global__ void __launch_bounds__(256) k_export_at(const int32_t* __restrict__ gidx,
-                                                   const double* __restrict__ gcoef, int64_t G,
-                                                   int kg, int d, const int64_t* __restrict__ pts,
-                                                   int64_t np_, int32_t* __restrict__ oidx,
-                                                   double* __restrict__ ocoef,
-                                                   const int32_t* __restrict__ nbase,
-                                                   const double* __restrict__ ncoef, int64_t M,
-                                                   int64_t ms, int bn,
-                                                   const int64_t* __restrict__ nds, int64_t nn,
-                                                   int32_t* __restrict__ obase,
-                                                   double* __restrict__ oncoef,
-                                                   int32_t* __restrict__ bad) {
+// Stored stencils of selected nodes nds[t], for inspection; an index out of
+// range sets *bad and is skipped.
+__global__ void __launch_bounds__(256) k_export_nodes(const int32_t* __restrict__ nbase,
+                                                      const double* __restrict__ ncoef, int64_t M,
+                                                      int64_t ms, int rows,
+                                                      const int64_t* __restrict__ nds, int64_t nn,
+                                                      int32_t* __restrict__ obase,
+                                                      double* __restrict__ oncoef,
+                                                      int32_t* __restrict__ bad) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < np_) {
-    const int64_t p = pts[t];
-    if (p < 0 || p >= G) {
-      *bad = 1;
-    } else {
-      for (int i = 0; i < kg; ++i) {
-        if (oidx) oidx[(int64_t)i * np_ + t] = gidx[(int64_t)i * G + p];
-        if (ocoef)
-          for (int a = 0; a < d; ++a)
-            ocoef[((int64_t)a * kg + i) * np_ + t] = gcoef[((int64_t)a * kg + i) * G + p];
-      }
-    }
+  if (t >= nn) return;
+  const int64_t n = nds[t];
+  if (n < 0 || n >= M) {
+    *bad = 1;
+    return;
   }
-  if (t < nn) {
-    const int64_t n = nds[t];
-    if (n < 0 || n >= M) {
-      *bad = 1;
-    } else {
-      if (obase) {
-        const int32_t v = nbase[n];
-        obase[t] = v < 0 ? ~v : v;
-      }
-      if (oncoef && ncoef)
-        for (int r = 0; r < d * bn; ++r) oncoef[(int64_t)r * nn + t] = ncoef[(int64_t)r * ms + n];
-    }
+  if (obase) {
+    const int32_t v = nbase[n];
+    obase[t] = v < 0 ? ~v : v;
   }
+  if (oncoef && ncoef)
+    for (int r = 0; r < rows; ++r) oncoef[(int64_t)r * nn + t] = ncoef[(int64_t)r * ms + n];
 }
 
 int scan_exclusive(const int32_t* in, int64_t n, int32_t* out, hipStream_t s) {
@@ -1119,7 +1288,7 @@ unsigned nblocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void geom_free(pc_geom* g) {
   if (!g) return;
-  void* ptrs[] = {g->gidx,   g->gcoef,  g->gcoef32, g->nbase,  g->ncoef,  g->ncoef32,
+  void* ptrs[] = {g->gblk,   g->gcnt,   g->grow,   g->gcoef,  g->gcoef32, g->nbase,   g->ncoef,  g->ncoef32,
                   g->ib,     g->near,   g->nslot,   g->ncoefib, g->ncoefib32, g->ibbase,
                   g->ibcoef, g->ibcoef32, g->sidx,  g->scoef,   g->scoef32,  g->vlist,
                   g->perm,   g->xyz,    g->ibx};
@@ -1140,19 +1309,23 @@ struct Scratch {
 
 // Device bytes held by a geometry with these counts (the arrays of
 // pc_wls_build; the node permutation of PC_ORDER_CELL not included).
-int64_t geom_bytes_for(int d, int64_t G, int64_t M, int k_grid, int bn, bool fit, int64_t n_ib,
+int64_t geom_bytes_for(int d, const int32_t* n, int64_t G, int64_t M, int k_grid, int bn, bool fit, int64_t n_ib,
                        int64_t n_near, int near_w, bool want64, bool want32, int k_self,
                        int64_t n_v) {
   const int64_t ms = (M + 63) / 64 * 64, ibs = (n_ib + 63) / 64 * 64;
   const int64_t ell = n_near ? (int64_t)near_w * ((n_near + 63) / 64 * 64) : 0;
   // indices, bases and lists (every geometry)
-  int64_t bytes = (int64_t)k_grid * G * 4 + M * 4 + n_ib * 4 + n_near * 4 + ell * 4 +
+  const int64_t ntile = grid_tiles(d, n), GT = ntile * tile_points(d);
+  const bool rows = grid_rows_kept(d, G, M);
+  int64_t bytes = (int64_t)k_grid * GT * 4 + ntile * 4 + M * 4 + n_ib * 4 + n_near * 4 + ell * 4 +
                   n_ib * 4 + (int64_t)k_self * ms * 4 + n_v * 4;
-  if (fit) bytes += (int64_t)d * (ms + ibs) * 8;  // positions
+  // grid rows and positions, float64 in every geometry
+  bytes += (rows ? (int64_t)grid_rows(d) * GT * 8 : 0) + (int64_t)d * (ms + (fit ? ibs : 0)) * 8;
   // coefficients, per kept precision (s bytes a value)
   for (int s : {8, 4}) {
     if (!(s == 8 ? want64 : want32)) continue;
-    bytes += ((int64_t)d * k_grid * G + (fit ? 0 : (int64_t)d * bn * (ms + ibs)) + ell * d +
+    bytes += ((rows ? 0 : (int64_t)d * k_grid * GT) +
+              (fit ? 0 : (int64_t)d * bn * (ms + ibs)) + ell * d +
               (int64_t)k_self * ms * (d + 1)) * s;
   }
   return bytes;
@@ -1338,17 +1511,30 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   PC_HIP_CHECK(hipGetLastError());
 
   // grid-target stencils
-  PC_TRY(dev_alloc((void**)&g->gidx, (size_t)k_grid * G * 4, "grid stencil indices"));
-  if (want64)
-    PC_TRY(dev_alloc((void**)&g->gcoef, (size_t)d * k_grid * G * 8, "grid stencil coefficients"));
-  if (want32)
-    PC_TRY(dev_alloc((void**)&g->gcoef32, (size_t)d * k_grid * G * 4, "grid stencil f32"));
+  const int64_t ntile = grid_tiles(d, P->n);
+  const int TP = tile_points(d);
+  if (ntile > INT32_MAX) return fail(PC_ERR_UNSUPPORTED_SIZE, "grid tiles");
+  PC_TRY(dev_alloc((void**)&g->gblk, (size_t)ntile * k_grid * TP * 4, "grid stencil indices"));
+  PC_TRY(dev_alloc((void**)&g->gcnt, (size_t)ntile * 4, "grid tile counts"));
+  g->gfit = grid_rows_kept(d, G, M);
+  if (g->gfit) {
+    PC_TRY(dev_alloc((void**)&g->grow, (size_t)ntile * grid_rows(d) * TP * 8, "grid stencil rows"));
+  } else {
+    const size_t nc = (size_t)ntile * d * k_grid * TP;
+    if (want64) PC_TRY(dev_alloc((void**)&g->gcoef, nc * 8, "grid stencil coefficients"));
+    if (want32) PC_TRY(dev_alloc((void**)&g->gcoef32, nc * 4, "grid stencil f32"));
+  }
   const RingArgs ring{xyz, M, gd, start, sorted};
-  GridStencilArgs ga{ring, k_grid, eps, support * delta, g->gidx, g->gcoef, g->gcoef32, bad};
-  if (d == 2)
-    hipLaunchKernelGGL(k_grid_stencils<2>, dim3(nblocks(G, 64)), dim3(64), 0, s, ga);
-  else
-    hipLaunchKernelGGL(k_grid_stencils<3>, dim3(nblocks(G, 64)), dim3(64), 0, s, ga);
+  const GridStencilArgs ga{ring, k_grid, eps, support * delta, grid_fit_args(g), g->gblk, g->grow,
+                           g->gcoef, g->gcoef32, bad};
+  const dim3 sg((unsigned)(ntile * (TP / 64)));
+  if (d == 2) {
+    if (g->gfit) hipLaunchKernelGGL((k_grid_stencils<2, true>), sg, dim3(64), 0, s, ga);
+    else hipLaunchKernelGGL((k_grid_stencils<2, false>), sg, dim3(64), 0, s, ga);
+  } else {
+    if (g->gfit) hipLaunchKernelGGL((k_grid_stencils<3, true>), sg, dim3(64), 0, s, ga);
+    else hipLaunchKernelGGL((k_grid_stencils<3, false>), sg, dim3(64), 0, s, ga);
+  }
   PC_HIP_CHECK(hipGetLastError());
 
   // node-target stencils
@@ -1357,12 +1543,14 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   g->fit = fit_lines(k_node, bn, m);
   g->hsup = support * delta;
   g->eps = eps;
+  PC_TRY(dev_alloc((void**)&g->xyz, (size_t)d * g->ms * 8, "node positions"));
+  PC_HIP_CHECK(hipMemcpy2DAsync(g->xyz, (size_t)g->ms * 8, xyz, (size_t)M * 8, (size_t)M * 8,
+                                (size_t)d, hipMemcpyDeviceToDevice, s));
   if (g->fit) {
-    PC_TRY(dev_alloc((void**)&g->xyz, (size_t)d * g->ms * 8, "node positions"));
     const NodeFit nf = node_fit_args(g);
 #define NFL(D, MB)                                                                            \
   hipLaunchKernelGGL((k_node_fit<D, MB>), dim3(nblocks(M, 256)), dim3(256), 0, s, xyz, M, gd, nf, \
-                     g->nbase, g->xyz, g->ms, bad)
+                     g->nbase, bad)
     if (d == 2) {
       if (m == 3) NFL(2, 3); else NFL(2, 4);
     } else {
@@ -1412,6 +1600,20 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
     return fail(PC_ERR_SINGULAR_STENCIL, "a WLS normal matrix is singular (squared pivot ratio "
                                          "below 1e-12)");
 
+  // tile lists (every grid point has its k_grid nodes: the flags are clear)
+  const GridFit gf = grid_fit_args(g);
+  int32_t* gmax = bad + 1;
+  if (!g->gfit)
+    PC_HIP_CHECK(hipMemsetAsync(g->gcnt, 0xff, (size_t)ntile * 4, s));
+  else if (d == 2)
+    hipLaunchKernelGGL(k_tile_pack<2>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk, g->gcnt,
+                       gmax);
+  else
+    hipLaunchKernelGGL(k_tile_pack<3>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk, g->gcnt,
+                       gmax);
+  PC_HIP_CHECK(hipGetLastError());
+  PC_HIP_CHECK(hipMemcpyAsync(&g->gmax, gmax, 4, hipMemcpyDeviceToHost, s));
+
   // boundary + virtual node list (ascending)
   std::vector<uint8_t> hkind((size_t)M);
   PC_HIP_CHECK(hipMemcpy(hkind.data(), kind, (size_t)M, hipMemcpyDeviceToHost));
@@ -1430,8 +1632,12 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   // near-IB grid points and their compact stencils
   uint8_t* nflag;
   PC_TRY(tmp.alloc((void**)&nflag, (size_t)G, "near flags"));
-  hipLaunchKernelGGL(k_near_flags, dim3(nblocks(G, 256)), dim3(256), 0, s, g->gidx, G, k_grid,
-                     kind, nflag);
+  if (d == 2)
+    hipLaunchKernelGGL(k_near_flags<2>, dim3((unsigned)(ntile * TP / 256)), dim3(256), 0, s, gf,
+                       kind, ntile, nflag);
+  else
+    hipLaunchKernelGGL(k_near_flags<3>, dim3((unsigned)(ntile * TP / 256)), dim3(256), 0, s, gf,
+                       kind, ntile, nflag);
   PC_HIP_CHECK(hipGetLastError());
   std::vector<uint8_t> hflag((size_t)G);
   PC_HIP_CHECK(hipMemcpyAsync(hflag.data(), nflag, (size_t)G, hipMemcpyDeviceToHost, s));
@@ -1469,14 +1675,14 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
     PC_HIP_CHECK(hipMemsetAsync(slot, 0xff, (size_t)M * 4, s));
     hipLaunchKernelGGL(k_slot_map, dim3(nblocks(g->n_ib, 256)), dim3(256), 0, s, g->ib, g->n_ib,
                        slot);
-    if (want64)
-      hipLaunchKernelGGL(k_near_fill<double>, dim3(nblocks(g->n_near, 256)), dim3(256), 0, s,
-                         g->near, g->n_near, g->nns, near_w, g->gidx, g->gcoef, G, k_grid, d,
-                         slot, g->nslot, g->ncoefib);
-    if (want32)
-      hipLaunchKernelGGL(k_near_fill<float>, dim3(nblocks(g->n_near, 256)), dim3(256), 0, s,
-                         g->near, g->n_near, g->nns, near_w, g->gidx, g->gcoef32, G, k_grid,
-                         d, slot, g->nslot, g->ncoefib32);
+    if (d == 2)
+      hipLaunchKernelGGL(k_near_fill<2>, dim3(nblocks(g->n_near, 256)), dim3(256), 0, s, g->near,
+                         g->n_near, g->nns, near_w, gf, slot, g->nslot, g->ncoefib,
+                         g->ncoefib32);
+    else
+      hipLaunchKernelGGL(k_near_fill<3>, dim3(nblocks(g->n_near, 256)), dim3(256), 0, s, g->near,
+                         g->n_near, g->nns, near_w, gf, slot, g->nslot, g->ncoefib,
+                         g->ncoefib32);
     PC_HIP_CHECK(hipGetLastError());
   }
   if (g->n_ib) {
@@ -1502,7 +1708,7 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
     PC_HIP_CHECK(hipGetLastError());
   }
   PC_HIP_CHECK(hipStreamSynchronize(s));
-  g->bytes = geom_bytes_for(d, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near, g->near_w, want64, want32,
+  g->bytes = geom_bytes_for(d, P->n, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near, g->near_w, want64, want32,
                             k_self, g->n_v);
   return PC_OK;
 }
@@ -1596,8 +1802,8 @@ int pc_geom_export(const pc_geom* g, int32_t* gidx, double* gcoef, int32_t* nbas
       PC_HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
     return PC_OK;
   };
-  PC_TRY(cp(gidx, g->gidx, (size_t)g->k_grid * g->G * 4));
-  PC_TRY(cp(gcoef, g->gcoef, (size_t)g->d * g->k_grid * g->G * 8));
+  if (gidx) PC_TRY(launch_index_export(g, nullptr, g->G, gidx, g->G, nullptr, s));
+  if (gcoef) PC_TRY(launch_grid_export(g, nullptr, g->G, gcoef, g->G, nullptr, s));
   if (nbase && g->M) {
     hipLaunchKernelGGL(k_base_export, dim3(nblocks(g->M, 256)), dim3(256), 0, s, g->nbase, g->M,
                        nbase);
@@ -1635,7 +1841,7 @@ int pc_geom_footprint(const pc_plan* P, int64_t M, int64_t n_ib, int64_t n_near,
   // the near table is as wide as the most B+V entries of a near point: at
   // most k_grid, rounded up to the kernel's widths
   const int near_w = k_grid <= 8 ? 8 : (k_grid <= 16 ? 16 : (k_grid <= 27 && d == 3 ? 27 : 32));
-  const int64_t gb = geom_bytes_for(d, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64, want32,
+  const int64_t gb = geom_bytes_for(d, P->n, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64, want32,
                                     k_self, n_ib) + (cell ? M * 4 : 0);
   if (geom_bytes) *geom_bytes = gb;
   if (build_peak_bytes) *build_peak_bytes = gb + build_scratch_bytes(d, P->G, M, cell);
@@ -1688,17 +1894,24 @@ int pc_geom_export_at(const pc_geom* g, const int64_t* grid_pts, int64_t n_grid,
     return fail(PC_ERR_INVALID_ARG, "pc_geom_export_at: bad target list");
   if ((grid_coef || node_coef) && !g->has64)
     return fail(PC_ERR_INVALID_ARG, "the geometry holds float32 stencils only");
-  const int64_t n = std::max(n_grid, n_nodes);
-  if (n == 0) return PC_OK;
+  if (n_grid == 0 && n_nodes == 0) return PC_OK;
   hipStream_t s = as_stream(stream);
   Scratch tmp;
   int32_t* bad;
   PC_TRY(tmp.alloc((void**)&bad, 256, "flags"));
   PC_TRY(fill_zero(bad, 256, s));
-  hipLaunchKernelGGL(k_export_at, dim3(nblocks(n, 256)), dim3(256), 0, s, g->gidx, g->gcoef, g->G,
-                     g->k_grid, g->d, grid_pts, n_grid, grid_idx, grid_coef, g->nbase, g->ncoef,
-                     g->M, g->ms, g->bn, nodes, n_nodes, node_base, node_coef, bad);
-  PC_HIP_CHECK(hipGetLastError());
+  if (n_nodes) {
+    hipLaunchKernelGGL(k_export_nodes, dim3(nblocks(n_nodes, 256)), dim3(256), 0, s, g->nbase,
+                       g->ncoef, g->M, g->ms, g->d * g->bn, nodes, n_nodes, node_base, node_coef,
+                       bad);
+    PC_HIP_CHECK(hipGetLastError());
+  }
+  // the indices always: they check the targets
+  Scratch ti;
+  int32_t* gi = grid_idx;
+  if (!gi && n_grid) PC_TRY(ti.alloc((void**)&gi, (size_t)g->k_grid * n_grid * 4, "indices"));
+  PC_TRY(launch_index_export(g, grid_pts, n_grid, gi, n_grid, bad, s));
+  if (grid_coef) PC_TRY(launch_grid_export(g, grid_pts, n_grid, grid_coef, n_grid, bad, s));
   if (node_coef && g->fit)
     PC_TRY(launch_fit_export(g, nodes, n_nodes, node_coef, n_nodes, bad, s));
   int32_t hbad = 0;

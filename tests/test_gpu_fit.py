@@ -2,14 +2,17 @@
 coefficients, against the oracle's rows: node targets (pc_stencil.h's tensor
 fit) on every block shape, axis condition and placement it is chosen for, at
 the walls, across periodic faces, for nodes outside the box, with a support
-radius below the block's, and on anisotropic grids."""
+radius below the block's, and on anisotropic grids; grid targets (quadratics
+applied to a tile's nodes in LDS) on grids that end inside a tile, with small
+and large stencils, with clusters too dense for a tile's list, and the stored
+coefficients that clouds much finer than the grid keep."""
 import numpy as np
 import pytest
 
 from oracle import Grid
 from oracle import projection as P
 from paper_2304_14690_amd import inputs
-from tests.helpers import rel_l2, to_np
+from tests.helpers import rel_l2, stored_order, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +99,98 @@ def test_degenerate_weight_is_refused(pc):
                          torch.zeros(x.shape[1], dtype=torch.uint8, device="cuda"), 16, 16,
                          eps=eps)
         assert e.value.code == pc.PC_ERR_SINGULAR_STENCIL
+
+
+# n, nodes per cell and axis, bc, k_grid, support
+GRID = {
+    "2d_one_tile": ((10, 8), 1, (N, N), 16, 3.0),
+    "2d_ragged": ((66, 18), 1, (N, N), 12, 3.0),
+    "2d_k9_per": ((34, 10), 1, (PER, PER), 9, 3.0),
+    "2d_k32": ((32, 24), 1, (PER, N), 32, 0.7),
+    "2d_fine_cloud": ((34, 16), 2, (N, N), 16, 3.0),
+    "2d_stored": ((34, 16), 3, (N, PER), 16, 3.0),
+    "2d_stored_k20": ((10, 12), 4, (PER, N), 20, 3.0),
+    "3d_ragged": ((18, 10, 8), 1, (N, N, N), 27, 3.0),
+    "3d_k16_per": ((8, 14, 10), 1, (PER, N, PER), 16, 3.0),
+    "3d_k32": ((16, 8, 12), 1, (N, N, N), 32, 3.0),
+    "3d_stored": ((18, 10, 8), 2, (N, N, PER), 27, 3.0),
+    "3d_stored_k20": ((8, 8, 10), 2, (N, PER, N), 20, 3.0),
+}
+
+
+@pytest.mark.parametrize("name", list(GRID))
+def test_grid_rows(pc, name):
+    import torch
+    n, ratio, bc, kg, support = GRID[name]
+    d = len(n)
+    h = (0.125,) * d
+    grid = Grid(d, n, h, bc)
+    delta = h[0] / ratio
+    x = inputs.jittered_lattice(tuple(v * ratio for v in n), (delta,) * d, 8, 0.3)
+    kind = np.zeros(x.shape[1], np.uint8)
+    kind[::11] = inputs.KIND_B
+    kn = 16 if d == 2 else 27
+    st = P.build_stencils(grid, x.T.copy(), kind, kg, kn, support=support, delta=delta)
+    assert not st.singular_grid.any()
+    plan = pc.Plan(d, n, h, bc=bc)
+    geom = pc.wls_build(plan, torch.from_numpy(x.copy()).cuda(), torch.from_numpy(kind).cuda(),
+                        kg, kn, support=support, delta=delta, want_f32=True)
+    G = grid.G
+    gi = torch.empty((kg, G), dtype=torch.int32, device="cuda")
+    gc = torch.empty((d, kg, G), dtype=torch.float64, device="cuda")
+    near = torch.empty(geom.n_near, dtype=torch.int32, device="cuda")
+    pc.geom_export(geom, gi, gc, near=near)
+    order = stored_order(grid, x.T, st.grid_idx)
+    np.testing.assert_array_equal(to_np(gi).T, np.take_along_axis(st.grid_idx, order, 1))
+    np.testing.assert_array_equal(to_np(near), st.near)
+    ref_c = np.take_along_axis(st.grid_coef, order[:, None, :], 2)
+    assert rel_l2(np.transpose(to_np(gc), (2, 0, 1)), ref_c) <= 1e-12
+    pts = torch.tensor([G - 1, 0, G // 2 + 3], dtype=torch.int64, device="cuda")
+    ci = torch.empty((kg, 3), dtype=torch.int32, device="cuda")
+    cc = torch.empty((d, kg, 3), dtype=torch.float64, device="cuda")
+    pc.geom_export_at(geom, pts, ci, cc)
+    assert torch.equal(ci, gi[:, pts]) and torch.equal(cc, gc[:, :, pts])
+    rng = np.random.Generator(np.random.PCG64(4))
+    u = rng.standard_normal(x.shape)
+    ib = np.flatnonzero(kind)
+    for dt in (torch.float64, torch.float32):
+        ut = torch.from_numpy(u).to(dt).cuda()
+        uh = to_np(ut).astype(np.float64)
+        b = torch.full((G,), 7.0, dtype=dt, device="cuda")
+        pc.div_to_grid(geom, ut, b)
+        ref = P.div_to_grid(st, uh.T)
+        # float32 fields: float64 coefficients and sums and one rounding, or
+        # rounded stored coefficients and k float32 sums of differences
+        stored = name.startswith(("2d_stored", "3d_stored"))
+        tol32 = 3 * kg * 2.0 ** -24 if stored else 2.0 ** -24
+        assert rel_l2(to_np(b), ref) <= (1e-12 if dt == torch.float64 else tol32)
+        # near-IB subset: the same rows on the B nodes only
+        bn = torch.zeros(G, dtype=dt, device="cuda")
+        pc.div_to_grid(geom, ut[:, ib].contiguous(), bn, pc.PC_NEAR_IB)
+        refn = P.div_to_grid(st, np.where(kind != 0, uh, 0.0).T)
+        # float32: rounded coefficients and 32 float32 sums of random values
+        assert rel_l2(to_np(bn), refn) <= (1e-12 if dt == torch.float64 else 32 * 2.0 ** -24)
+
+
+def test_dense_cluster(pc):
+    """A cloud of ordinary density with one cluster: the tiles around it have
+    more nodes than their lists hold and gather from memory, the others not."""
+    import torch
+    n, h = (64, 24), (1.0 / 64,) * 2
+    x = inputs.jittered_lattice(n, h, 8, 0.3)
+    # a 45 x 45 patch of nodes over 7 x 7 cells inside one tile, and its surroundings
+    c = inputs.jittered_lattice((56, 56), (h[0] / 8,) * 2, 9, 0.3)
+    x = np.concatenate([x, c + np.array([[8 * h[0]], [8 * h[1]]])], axis=1)
+    kind = np.zeros(x.shape[1], np.uint8)
+    grid = Grid(2, n, h)
+    st = P.build_stencils(grid, x.T.copy(), kind, 32, 16)
+    # nodes in use by the tile of 32 x 8 points that holds the cluster
+    cc = grid.centres() / h[0]
+    tile = (cc[:, 0] < 32) & (cc[:, 1] >= 8) & (cc[:, 1] < 16)
+    print("nodes of the tile:", np.unique(st.grid_idx[tile]).size)
+    plan = pc.Plan(2, n, h)
+    geom = pc.wls_build(plan, torch.from_numpy(x).cuda(), torch.from_numpy(kind).cuda(), 32, 16)
+    u = np.random.Generator(np.random.PCG64(4)).standard_normal(x.shape)
+    b = torch.empty(grid.G, dtype=torch.float64, device="cuda")
+    pc.div_to_grid(geom, torch.from_numpy(u).cuda(), b)
+    assert rel_l2(to_np(b), P.div_to_grid(st, u.T)) <= 1e-11
