@@ -790,7 +790,22 @@ int generic_radices(int H, int* rad) {
 
 bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
-int rad_values(int N) {
+// Radix 4 where a pass is bound by a wavefront's own instructions and latency
+// rather than by the device: on every axis of grids of up to 2^20 points, which
+// leave the radix-8 plan at most one wavefront per SIMD (N up to 1024 on the
+// fused last axis, 512 on a middle one), and on larger grids for the x rows and
+// middle axes, whose IB-iteration launches touch a few lines only.  The fused
+// last axis of larger grids is faster with radix 8 (256^3: 88 against 105 us),
+// and so is a middle axis above 256 points, whose tiles would shrink below
+// 64 bytes of adjacent lines (512^3 float32 solve: 1.19 against 1.30 ms).
+// Sub-steps, radix 8 -> this rule: 64^2 240 -> 223 us, 512^2 231 -> 216,
+// 1024^2 311 -> 305, 2048^2 617 -> 587, 64^3 280 -> 260, 128^3 544 -> 514
+// (mixed 897 -> 844), 256^3 2.75 -> 2.71 ms.
+int rad_values(const pc_plan* P, int axis) {
+  const int N = P->n[axis];
+  const bool small = P->G <= (int64_t)1 << 20;
+  const int lim4 = axis == 0 ? 2048 : (axis < P->d - 1 ? (small ? 512 : 256) : (small ? 1024 : 0));
+  if (N >= 32 && N <= lim4 && pow2(N)) return 4;
   if (N >= 32 && N <= 4096 && pow2(N)) return 8;
   if (N == 200 || N == 400 || N == 1000 || N == 2000) return 10;
   return 0;
@@ -809,7 +824,7 @@ int floor_pow2(int v) {
 // the axis uses the generic kernel: N < 32 or not a power of two).
 int rad_tile_lines(const pc_plan* P, int axis, size_t elem) {
   const int N = P->n[axis];
-  const int RT = rad_values(N);
+  const int RT = rad_values(P, axis);
   if (!RT) return 0;
   const int H = N / 2, T = H / RT, LS = H + H / 16 + 1;
   const int64_t lines = P->G / N;
@@ -864,7 +879,7 @@ PassTiles pass_tiles(const pc_plan* P, int axis, size_t elem) {
   PassTiles pt{};
   const int N = P->n[axis];
   const int64_t lines = P->G / N;
-  const bool reg = rad_values(N) != 0;
+  const bool reg = rad_values(P, axis) != 0;
   const bool masked = !reg && P->bc[axis] == PC_BC_PERIODIC;
   pt.C = reg ? rad_tile_lines(P, axis, elem) : generic_tile_lines(P, axis, elem, nullptr, nullptr);
   if (axis == 0) {
@@ -968,7 +983,7 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     PC_HIP_CHECK(hipGetLastError());
     return PC_OK;
   }
-  if (const int RT = rad_values(A.N)) {
+  if (const int RT = rad_values(P, axis)) {
     // register kernel: T = H/RT threads per line, C lines per group
     const int T = H / RT;
     const int LS = H + H / 16 + 1;
@@ -992,7 +1007,7 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     // the row residual loader stages the tile's float64 phi in the same LDS
     if (LD == LD_RESID && axis == 0) lds = std::max(lds, (size_t)C * A.N * sizeof(double));
     if (lds > (size_t)lds_limit()) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform tile does not fit in LDS");
-    const int key = (RT == 8 ? logH : H) * 32 + RT;
+    const int key = (RT == 10 ? H : logH) * 32 + RT;
     if (P->bc[axis] == PC_BC_PERIODIC)
       return rad_launch<TC, TI, TO, OP, LD, ST, true>(A, key, dim3(ntile), dim3(C * T), lds, s);
     return rad_launch<TC, TI, TO, OP, LD, ST, false>(A, key, dim3(ntile), dim3(C * T), lds, s);

@@ -1,5 +1,5 @@
 // Line-transform kernels shared by the translation units that instantiate
-// them: the register-resident radix-8 transforms of one grid axis, as a
+// them: the register-resident radix-8, radix-4 and radix-10 transforms of one grid axis, as a
 // cosine transform (homogeneous Neumann condition, Eq. 7) or as a packed
 // real Fourier transform (periodic axis), and the argument block of every
 // transform launch.  Included by pc_solve.hip (Neumann axes) and
@@ -403,6 +403,7 @@ __device__ __forceinline__ void line_sync() {
 template <typename TC>
 struct R8Tw {
   cplx<TC> s1, s2, fin;
+  cplx<TC> s3, s4;  // radix-4 plan: the bases for L = 64, 256 (s1, s2: L = 4, 16)
 };
 
 // v[r] *= w^r, r = 1..7, with the powers built by squaring (each power is at
@@ -490,6 +491,57 @@ __device__ __forceinline__ void r8_fft(cplx<TC>* a, int t, const R8Tw<TC>& tw,
   if (RR == 2) rad_final<TC, INV, 8, 2>(a, T, tw.fin, twH);
 }
 
+// ---- radix-4 plan (4 values per thread, T = H/4 threads per line) -------------
+// The same Stockham FFT with half the values and half the arithmetic per
+// thread and one or two exchanges more, where a pass takes what one
+// wavefront's chain of instructions takes (rad_values): the passes of the
+// 64^2 grid, 4-8 us with radix 8, take 3.2-5.9 us.
+
+template <typename TC, bool INV, bool LAST, int T>
+__device__ __forceinline__ void r4_stage(cplx<TC>* a, int t, int L, cplx<TC> w, cplx<TC>* z) {
+  cplx<TC> v[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = a[r];
+  if (L > 1) {
+    const cplx<TC> w2 = cmul(w, w), w3 = cmul(w2, w);
+    v[1] = INV ? cmulc(v[1], w) : cmul(v[1], w);
+    v[2] = INV ? cmulc(v[2], w2) : cmul(v[2], w2);
+    v[3] = INV ? cmulc(v[3], w3) : cmul(v[3], w3);
+  }
+  dft4<TC, INV>(v[0], v[1], v[2], v[3]);
+  if (LAST) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = v[r];
+  } else {
+    // base mod 16 + r L mod 16 < 16 (lpad_scatter): L = 1 with base a
+    // multiple of 4, L = 4 with base = k < 4 mod 16, or L a multiple of 16
+    const int k = t & (L - 1);
+    const int lb = lpad((t - k) * 4 + k);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z[lpad_scatter(lb, r * L)] = v[r];
+    line_sync<T>();
+    const int lt = lpad(t);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = z[lpad_tq<T>(t, lt, q)];
+    line_sync<T>();
+  }
+}
+
+template <typename TC, bool INV, int LOGH>
+__device__ __forceinline__ void r4_fft(cplx<TC>* a, int t, const R8Tw<TC>& tw,
+                                       const cplx<TC>* __restrict__ twH, cplx<TC>* z) {
+  constexpr int T = (1 << LOGH) / 4;
+  constexpr int S4 = LOGH / 2;         // radix-4 stages
+  constexpr int RR = 1 << (LOGH % 2);  // final radix (1: none)
+  static_assert(S4 >= 2 && S4 <= 5, "radix-4 plan covers 16 <= H <= 2048");
+  r4_stage<TC, INV, false, T>(a, t, 1, tw.s1, z);
+  r4_stage<TC, INV, (S4 == 2 && RR == 1), T>(a, t, 4, tw.s1, z);
+  if (S4 >= 3) r4_stage<TC, INV, (S4 == 3 && RR == 1), T>(a, t, 16, tw.s2, z);
+  if (S4 >= 4) r4_stage<TC, INV, (S4 == 4 && RR == 1), T>(a, t, 64, tw.s3, z);
+  if (S4 >= 5) r4_stage<TC, INV, (RR == 1), T>(a, t, 256, tw.s4, z);
+  if (RR == 2) rad_final<TC, INV, 4, 2>(a, T, tw.fin, twH);
+}
+
 // ---- radix-10 plan (10 values per thread, T = H/10 threads per line) ----------
 // For H = 10^s f with f = 1, 2 or 5 (the n/2 = 200 and 1000 of the 400 and
 // 2000 point grids of Sec. 3): s radix-10 Stockham stages (L = 1, 10, 100),
@@ -560,10 +612,11 @@ __device__ __forceinline__ void r10_fft(cplx<TC>* a, int t, const R8Tw<TC>& tw,
 }
 
 // The register kernels' half-length H from the length code HL of their
-// template: log2(H) for the radix-8 plan, H itself for the radix-10 plan.
+// template: log2(H) for the radix-8 and radix-4 plans, H itself for the
+// radix-10 plan.
 template <int HL, int RT>
 struct RadLen {
-  static constexpr int H = RT == 8 ? (1 << HL) : HL;
+  static constexpr int H = RT == 10 ? HL : (1 << HL);
 };
 
 // Twiddle state of either plan for thread t of a line.
@@ -574,6 +627,12 @@ __device__ __forceinline__ R8Tw<TC> rad_twiddles(const cplx<TC>* __restrict__ tw
     if (H >= 64) tw.s1 = twH[(H / 64) * (t & 7)];
     if (H >= 512) tw.s2 = twH[(H / 512) * (t & 63)];
     if (__builtin_ctz(H) % 3) tw.fin = twH[t];
+  } else if constexpr (RT == 4) {
+    tw.s1 = twH[(H / 16) * (t & 3)];
+    if (H >= 64) tw.s2 = twH[(H / 64) * (t & 15)];
+    if (H >= 256) tw.s3 = twH[(H / 256) * (t & 63)];
+    if (H >= 1024) tw.s4 = twH[(H / 1024) * (t & 255)];
+    if (__builtin_ctz(H) % 2) tw.fin = twH[t];
   } else {
     constexpr int S = R10Plan<H>::S, F = R10Plan<H>::F;
     if (S >= 2) tw.s1 = twH[(H / 100) * (t % 10)];
@@ -586,8 +645,10 @@ __device__ __forceinline__ R8Tw<TC> rad_twiddles(const cplx<TC>* __restrict__ tw
 template <typename TC, bool INV, int H, int RT>
 __device__ __forceinline__ void rad_fft(cplx<TC>* a, int t, const R8Tw<TC>& tw8,
                                         const cplx<TC>* __restrict__ twH, cplx<TC>* z) {
-  static_assert(RT == 8 || RT == 10, "the register kernels run radix-8 or radix-10 plans");
-  if constexpr (RT == 8)
+  static_assert(RT == 4 || RT == 8 || RT == 10, "radix-4, radix-8 or radix-10 plan");
+  if constexpr (RT == 4)
+    r4_fft<TC, INV, __builtin_ctz(H)>(a, t, tw8, twH, z);
+  else if constexpr (RT == 8)
     r8_fft<TC, INV, __builtin_ctz(H)>(a, t, tw8, twH, z);
   else
     r10_fft<TC, INV, H>(a, t, tw8, twH, z);
@@ -671,8 +732,8 @@ __device__ __forceinline__ int xpad(int r) { return r + 2 * (r >> 5); }
 
 // One pass of the line transforms over a tile of C lines: forward (OP_FWD),
 // inverse (OP_INV), or forward, division by the eigenvalues and inverse
-// along the last axis (OP_FDI).  RT = 8 (radix-8 plan) or 10 (radix-10
-// plan) complex values per thread, T = H / RT threads per line.
+// along the last axis (OP_FDI).  RT = 8 (radix-8 plan), 4 (radix-4 plan)
+// or 10 (radix-10 plan) complex values per thread, T = H / RT threads per line.
 //   PER = false: DCT-II forward, DCT-III / (2N) inverse (Neumann axis).
 //   PER = true:  packed real DFT of a periodic axis, in the same slots:
 //                slot k = Re X_k (k < H), slot N-k = Im X_k (0 < k < H),
@@ -856,7 +917,7 @@ dct_rad(LineArgs<TC> A) {
     for (int q = 0; q < RT; ++q) {
       const int k = t + T * q;
       cplx<TC> Zk = a[q];
-      cplx<TC> Zc = conj_(z[lpad(RT == 8 ? (H - k) & (H - 1) : (k ? H - k : 0))]);
+      cplx<TC> Zc = conj_(z[lpad(RT != 10 ? (H - k) & (H - 1) : (k ? H - k : 0))]);
       // twice the even/odd split E, D (and O = -i D): the cosine transform's
       // factor 2 absorbs the halving (scaling by powers of two is exact; the
       // results differ from halving first only where the compiler fuses
@@ -1032,6 +1093,8 @@ dct_rad(LineArgs<TC> A) {
     // which halves the occupancy
     asm volatile("" : "+v"(tw8.s1.re), "+v"(tw8.s1.im), "+v"(tw8.s2.re), "+v"(tw8.s2.im));
     asm volatile("" : "+v"(tw8.fin.re), "+v"(tw8.fin.im));
+    if constexpr (RT == 4 && H >= 256) asm volatile("" : "+v"(tw8.s3.re), "+v"(tw8.s3.im));
+    if constexpr (RT == 4 && H >= 1024) asm volatile("" : "+v"(tw8.s4.re), "+v"(tw8.s4.im));
   }
   int ti = t, zoff = c * LS;
   asm volatile("" : "+v"(ti));
@@ -1078,7 +1141,7 @@ dct_rad(LineArgs<TC> A) {
 }
 
 // Launches dct_rad<..., PER> for the transform length and radix of `key`
-// (HL * 32 + RT, HL = log2(H) for RT = 8 and H for RT = 10) on `grid`
+// (HL * 32 + RT, HL = log2(H) for RT = 8 or 4 and H for RT = 10) on `grid`
 // workgroups of `block` threads.
 template <typename TC, typename TI, typename TO, int OP, int LD, int ST, bool PER>
 int rad_launch(const LineArgs<TC>& A, int key, dim3 grid, dim3 block, size_t lds,
@@ -1087,6 +1150,8 @@ int rad_launch(const LineArgs<TC>& A, int key, dim3 grid, dim3 block, size_t lds
   switch (key) {
 #define PC_RAD_CASE(LH, R) \
     case LH * 32 + R: fn = (const void*)dct_rad<TC, TI, TO, OP, LD, ST, LH, R, PER>; break;
+    PC_RAD_CASE(4, 4) PC_RAD_CASE(5, 4) PC_RAD_CASE(6, 4) PC_RAD_CASE(7, 4) PC_RAD_CASE(8, 4)
+    PC_RAD_CASE(9, 4) PC_RAD_CASE(10, 4)
     PC_RAD_CASE(4, 8) PC_RAD_CASE(5, 8) PC_RAD_CASE(6, 8) PC_RAD_CASE(7, 8)
     PC_RAD_CASE(8, 8) PC_RAD_CASE(9, 8) PC_RAD_CASE(10, 8) PC_RAD_CASE(11, 8)
     PC_RAD_CASE(100, 10) PC_RAD_CASE(200, 10) PC_RAD_CASE(500, 10) PC_RAD_CASE(1000, 10)
@@ -1100,6 +1165,8 @@ int rad_launch(const LineArgs<TC>& A, int key, dim3 grid, dim3 block, size_t lds
     case LH * 32 + R: \
       hipLaunchKernelGGL((dct_rad<TC, TI, TO, OP, LD, ST, LH, R, PER>), grid, block, lds, s, A); \
       break;
+    PC_RAD_LAUNCH(4, 4) PC_RAD_LAUNCH(5, 4) PC_RAD_LAUNCH(6, 4) PC_RAD_LAUNCH(7, 4)
+    PC_RAD_LAUNCH(8, 4) PC_RAD_LAUNCH(9, 4) PC_RAD_LAUNCH(10, 4)
     PC_RAD_LAUNCH(4, 8) PC_RAD_LAUNCH(5, 8) PC_RAD_LAUNCH(6, 8) PC_RAD_LAUNCH(7, 8)
     PC_RAD_LAUNCH(8, 8) PC_RAD_LAUNCH(9, 8) PC_RAD_LAUNCH(10, 8) PC_RAD_LAUNCH(11, 8)
     PC_RAD_LAUNCH(100, 10) PC_RAD_LAUNCH(200, 10) PC_RAD_LAUNCH(500, 10) PC_RAD_LAUNCH(1000, 10)
