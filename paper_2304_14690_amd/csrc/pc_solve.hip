@@ -33,6 +33,8 @@ namespace {
 // the thread cap for the strided (column/pencil) passes.
 constexpr int ROW_THREADS = 256;
 constexpr int COL_MAX_THREADS = 512;
+// Bytes of the generic kernels' twiddle copy, at most (lds_twiddles).
+constexpr size_t LTW_MAX = 512 * 8 + 16;
 
 // n / d for 0 <= n < 2^17 and 0 < d <= 2^16, with rinv = 1.0f / d: the
 // float32 product is within one of the quotient, and one correction step
@@ -62,6 +64,8 @@ __device__ __forceinline__ void mixed_bfly(const cplx<TC>* x, cplx<TC>* y, int g
     dft3<TC, INV>(v);
   else if constexpr (R == 5)
     dft5<TC, INV>(v);
+  else if constexpr (R == 7)
+    dft7<TC, INV>(v);
   else
     dftR<TC, INV, R>(v);
 #pragma unroll
@@ -74,13 +78,14 @@ __device__ __forceinline__ void mixed_bfly(const cplx<TC>* x, cplx<TC>* y, int g
 // of combined length L takes butterfly g (k = g mod L) of each line:
 //   v_s = in[g + (H/r) s] w^(k s),  w = exp(-+2 pi i / (L r)),
 //   out[(g - k) r + k + s' L] = sum_{s<r} v_s exp(-+2 pi i s s' / r),
-// with w^e = twH[(H / (L r)) e]; radices 2, 3, 4, 5 and 8 have their own
-// butterflies, any other prime factor (7, 67, ...) a direct sum of r terms
-// per output.  Returns the buffer holding the result (the stages alternate
-// between a and b).
+// with w^e = twH[(H / (L r)) e]; radices 2, 3, 4, 5, 7 and 8 have their own butterflies, any other prime
+// factor (11, 67, ...) a direct sum of r terms per output, its twiddles from
+// the LDS copy twl where A.ltw says there is one.  Returns the buffer holding
+// the result (the stages alternate between a and b).
 template <typename TC, bool INV>
-__device__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int lsc, int C, int H,
-                                   const LineArgs<TC>& A, int tid, int nthr) {
+__device__ __forceinline__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int lsc, int C, int H,
+                                                   const LineArgs<TC>& A, const cplx<TC>* twl,
+                                                   int tid, int nthr) {
   const cplx<TC>* __restrict__ twH = A.tab.twH;
   int L = 1;
   for (int st = 0; st < A.nrad; ++st) {
@@ -89,34 +94,49 @@ __device__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int lsc, int C, int
     const int Lr = L * r;
     const int tstep = H / Lr;
     const float rnb = 1.0f / (float)nb, rL = 1.0f / (float)L;
-    for (int e = tid; e < C * nb; e += nthr) {
-      const int c = div_small(e, nb, rnb);
-      const int g = e - c * nb;
-      const int k = g - L * div_small(g, L, rL);
-      const cplx<TC>* x = a + c * lsc;
-      cplx<TC>* y = b + c * lsc + (g - k) * r + k;
-      switch (r) {
-        case 2: mixed_bfly<TC, INV, 2>(x, y, g, nb, k, L, tstep, twH); break;
-        case 3: mixed_bfly<TC, INV, 3>(x, y, g, nb, k, L, tstep, twH); break;
-        case 4: mixed_bfly<TC, INV, 4>(x, y, g, nb, k, L, tstep, twH); break;
-        case 5: mixed_bfly<TC, INV, 5>(x, y, g, nb, k, L, tstep, twH); break;
-        case 8: mixed_bfly<TC, INV, 8>(x, y, g, nb, k, L, tstep, twH); break;
-        default: {
-          // direct sum: output s' takes v_s W_r^(s s'), W_r^m = twH[nb (m mod r)]
-          for (int sp = 0; sp < r; ++sp) {
-            cplx<TC> acc = x[g];
-            int ex = 0;            // (k + L s') s mod Lr, as in the twiddled DFT
+    auto stage = [&](auto radix) {
+      constexpr int R = decltype(radix)::value;
+      for (int e = tid; e < C * nb; e += nthr) {
+        const int c = div_small(e, nb, rnb);
+        const int g = e - c * nb;
+        const int k = g - L * div_small(g, L, rL);
+        mixed_bfly<TC, INV, R>(a + c * lsc, b + c * lsc + (g - k) * R + k, g, nb, k, L, tstep, twH);
+      }
+    };
+    switch (r) {
+      case 2: stage(std::integral_constant<int, 2>{}); break;
+      case 3: stage(std::integral_constant<int, 3>{}); break;
+      case 4: stage(std::integral_constant<int, 4>{}); break;
+      case 5: stage(std::integral_constant<int, 5>{}); break;
+      case 7: stage(std::integral_constant<int, 7>{}); break;
+      case 8: stage(std::integral_constant<int, 8>{}); break;
+      default: {
+        // a direct sum per output: output s' of butterfly g takes
+        // v_s W_r^(s s') with W_r^m = twH[nb (m mod r)]; a thread per output,
+        // since a large prime leaves few butterflies (n/2 = 201: three)
+        const float rH = 1.0f / (float)H;
+        auto sums = [&](const auto* tw) {
+          for (int e = tid; e < C * H; e += nthr) {
+            const int c = div_small(e, H, rH);
+            const int o = e - c * H;
+            const int sp = div_small(o, nb, rnb);
+            const int g = o - sp * nb;
+            const int k = g - L * div_small(g, L, rL);
+            const cplx<TC>* x = a + c * lsc + g;
+            cplx<TC> acc = x[0];
+            int ex = 0;  // (k + L s') s mod Lr, as in the twiddled DFT
             const int q = k + L * sp;
             for (int sidx = 1; sidx < r; ++sidx) {
               ex += q;
               if (ex >= Lr) ex -= Lr;
-              const cplx<TC> w = twH[tstep * ex];
-              const cplx<TC> v = x[g + nb * sidx];
+              const cplx<TC> w = tw[tstep * ex];
+              const cplx<TC> v = x[nb * sidx];
               acc = cadd(acc, INV ? cmulc(v, w) : cmul(v, w));
             }
-            y[sp * L] = acc;
+            b[c * lsc + (g - k) * r + k + sp * L] = acc;
           }
-        }
+        };
+        if (A.ltw) sums(twl); else sums(twH);
       }
     }
     __syncthreads();
@@ -126,6 +146,137 @@ __device__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int lsc, int C, int
     L = Lr;
   }
   return a;
+}
+
+// What bounds the generic kernels: on small grids the latency of each step (one
+// load at a time per thread, then a chain of table reads), on large ones LDS
+// and instruction issue.  Loads are batched, indices split without integer
+// division or 64-bit remainders, and a direct sum gives every output a thread
+// (one thread per butterfly left three threads busy on a 402-point line).
+// 402^2 float64 sub-step 12.3 ms -> 562 us, 280 x 480 350 -> 280 us, 150 x 136
+// x 84 1.37 -> 0.90 ms; solves 1998 x 1540 748 -> 247 us (float32 periodic 806
+// -> 230), 190 x 184 x 176 float32 965 -> 305, 1040 x 1404 periodic 214 -> 115.
+
+// The points of a generic kernel's tile: element e < C N is point n of line c
+// (rows: the points of a line adjacent, the C lines contiguous in memory;
+// strided: C lines, a power of two, adjacent).
+struct GenTile {
+  int64_t p0;     // offset of element 0
+  int64_t stride;
+  int N, C, lc, nval;  // nval: lines inside the grid (a partial last tile)
+  bool rows;
+  float rN;
+  int i0, o0;     // line_base's coordinates of line 0
+  int32_t n1;
+  int axis;
+
+  __device__ __forceinline__ void split(int e, int* c, int* n) const {
+    if (rows) {
+      *c = div_small(e, N, rN);
+      *n = e - *c * N;
+    } else {
+      *n = e >> lc;
+      *c = e & (C - 1);
+    }
+  }
+  __device__ __forceinline__ int64_t at(int e, int c, int n) const {
+    return rows ? p0 + e : p0 + c + (int64_t)n * stride;
+  }
+  // cell of point n of line c
+  __device__ __forceinline__ void cell(int c, int n, int* i, int* j, int* k) const {
+    if (rows) {
+      const uint32_t l = (uint32_t)o0 + c;
+      *i = n;
+      *k = (int)(l / (uint32_t)n1);
+      *j = (int)(l - (uint32_t)*k * (uint32_t)n1);
+    } else {
+      *i = i0 + c;
+      *j = axis == 1 ? n : o0;
+      *k = axis == 1 ? o0 : n;
+    }
+  }
+};
+
+template <typename TC>
+__device__ __forceinline__ GenTile gen_tile(const LineArgs<TC>& A, int t) {
+  GenTile G;
+  G.rows = A.axis == 0;
+  G.p0 = line_base(A, t, 0, &G.i0, &G.o0);
+  G.stride = A.stride;
+  G.N = A.N;
+  G.C = A.C;
+  G.lc = __builtin_ctz(A.C);
+  G.rN = 1.0f / (float)A.N;
+  G.n1 = A.n1;
+  G.axis = A.axis;
+  G.nval = (int)min((int64_t)A.C, G.rows ? A.lines - (int64_t)t * A.C : (int64_t)(A.n0 - G.i0));
+  return G;
+}
+
+// for e = tid, tid + nthr, ... < total: st(e, ld(e)), U loads before their
+// stores, so that a thread waits for memory once per U elements.
+template <int U, typename V, typename LDF, typename STF>
+__device__ __forceinline__ void batched(int total, int tid, int nthr, const LDF& ld,
+                                        const STF& st) {
+  for (int e0 = tid; e0 < total; e0 += U * nthr) {
+    V v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * nthr < total) v[u] = ld(e0 + u * nthr);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * nthr < total) st(e0 + u * nthr, v[u]);
+  }
+}
+
+// Point e of a tile as the forward transforms load it (0 outside the grid).
+template <typename TC, typename TI, int LD, bool VERTEX>
+__device__ __forceinline__ TC gen_load(const LineArgs<TC>& A, const GenTile& G, const TI* in,
+                                       double sub, int e) {
+  int c, n;
+  G.split(e, &c, &n);
+  if (c >= G.nval) return TC(0);
+  const int64_t p = G.at(e, c, n);
+  if (LD == LD_RESID) {
+    int i, j, k;
+    G.cell(c, n, &i, &j, &k);
+    return (TC)(resid_ijk<VERTEX>(A.rb, A.rphi, p, i, j, k, A.d, A.n0, A.n1, A.n2, A.perm, A.ih2,
+                                  A.rscale) - sub);
+  }
+  return A.sub ? (TC)((double)in[p] - sub) : (TC)in[p];
+}
+
+// Element e of the result (ST_ACCUM: added to phi).
+template <typename TC, typename TO, int ST, typename RD>
+__device__ __forceinline__ void gen_store(const LineArgs<TC>& A, const GenTile& G, int tid,
+                                          int nthr, const RD& rd) {
+  TO* __restrict__ out = reinterpret_cast<TO*>(A.out);
+  batched<4, double>(
+      G.C * G.N, tid, nthr,
+      [&](int e) -> double {
+        if (ST != ST_ACCUM) return 0.0;
+        int c, n;
+        G.split(e, &c, &n);
+        return c < G.nval ? A.rphi[G.at(e, c, n)] : 0.0;
+      },
+      [&](int e, double old) {
+        int c, n;
+        G.split(e, &c, &n);
+        if (c >= G.nval) return;
+        const TC v = rd(c, n);
+        if (ST == ST_ACCUM)
+          reinterpret_cast<double*>(A.out)[G.at(e, c, n)] = old + (double)v;
+        else
+          out[G.at(e, c, n)] = (TO)v;
+      });
+}
+
+// Copies the half-length twiddles into LDS (A.ltw).
+template <typename TC>
+__device__ __forceinline__ void stage_twiddles(cplx<TC>* twl, const cplx<TC>* __restrict__ twH,
+                                               int H, int tid, int nthr) {
+  batched<2, cplx<TC>>(H, tid, nthr, [&](int e) { return twH[e]; },
+                       [&](int e, cplx<TC> w) { twl[e] = w; });
 }
 
 // Forward post-processing of pair k (0 <= k <= H/2) of one line: from the
@@ -180,31 +331,24 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
   const int N = A.N, H = N >> 1, C = A.C;
   const int ls = N + A.pad;  // line stride in LDS (reals)
   TC* s2 = s + (size_t)C * ls;  // second buffer
+  cplx<TC>* twl = reinterpret_cast<cplx<TC>*>(s2 + (size_t)C * ls);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int t = A.tiles ? A.tiles[blockIdx.x]
                         : (A.axis == 0 ? blockIdx.x : xcd_tile(blockIdx.x, gridDim.x));
   const TI* __restrict__ in = reinterpret_cast<const TI*>(A.in);
-  TO* __restrict__ out = reinterpret_cast<TO*>(A.out);
+  const GenTile G = gen_tile(A, t);
 
   // ---- load ----------------------------------------------------------------
-  for (int e = tid; e < C * N; e += nthr) {
-    int c, n;
-    if (A.axis == 0) { c = e / N; n = e - c * N; } else { n = e / C; c = e - n * C; }
-    int i, o;
-    int64_t p = line_base(A, t, c, &i, &o) + (int64_t)n * A.stride;
-    TC v;
-    if (LD == LD_RESID) {
-      double r = resid_at(A.rb, A.rphi, p, A.d, A.n0, A.n1, A.n2, A.perm, A.ih2, A.rscale);
-      if (A.sub) r -= *A.sub;
-      v = (TC)r;
-    } else if (A.sub) {
-      v = (TC)((double)in[p] - *A.sub);
-    } else {
-      v = (TC)in[p];
-    }
-    int q = (OP == OP_INV) ? n : mk_pos(n, N);
-    s[c * ls + q] = v;
-  }
+  const double sub = A.sub ? *A.sub : 0.0;
+  if (A.ltw) stage_twiddles(twl, A.tab.twH, H, tid, nthr);
+  batched<LD == LD_RESID ? 2 : 4, TC>(
+      C * N, tid, nthr,
+      [&](int e) { return gen_load<TC, TI, LD, false>(A, G, in, sub, e); },
+      [&](int e, TC v) {
+        int c, n;
+        G.split(e, &c, &n);
+        s[c * ls + (OP == OP_INV ? n : mk_pos(n, N))] = v;
+      });
   __syncthreads();
 
   cplx<TC>* zc = reinterpret_cast<cplx<TC>*>(s);
@@ -242,9 +386,9 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
       }
     }
     __syncthreads();
-    res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, tid, nthr));
+    res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
   } else {
-    const cplx<TC>* zf = fft_lds_mixed<TC, false>(zc, zc2, lsc, C, H, A, tid, nthr);
+    const cplx<TC>* zf = fft_lds_mixed<TC, false>(zc, zc2, lsc, C, H, A, twl, tid, nthr);
     constexpr int PB = 2 * B + 1;
     TC xa[PB], xb[PB], xc[PB], xd[PB];
     int ck[PB], kk[PB];
@@ -266,10 +410,8 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
       for (int b = 0; b < PB; ++b) {
         if (ck[b] >= 0) {
           int c = ck[b], k = kk[b];
-          int i, o;
-          (void)line_base(A, t, c, &i, &o);
-          TC rest = A.lam0[i];
-          if (A.lam1) rest += A.lam1[o];
+          TC rest = A.lam0[G.i0 + c];
+          if (A.lam1) rest += A.lam1[G.o0];
           const TC* lam = A.tab.lam;
           const TC ls_ = A.lscale;
           TC l0 = (rest + lam[k]) * ls_, l1 = (rest + lam[k ? N - k : 0]) * ls_,
@@ -297,7 +439,7 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
         }
       }
       __syncthreads();
-      res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, tid, nthr));
+      res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
     } else {
       __syncthreads();
 #pragma unroll
@@ -319,19 +461,9 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
   }
 
   // ---- store ----------------------------------------------------------------
-  for (int e = tid; e < C * N; e += nthr) {
-    int c, n;
-    if (A.axis == 0) { c = e / N; n = e - c * N; } else { n = e / C; c = e - n * C; }
-    int i, o;
-    int64_t p = line_base(A, t, c, &i, &o) + (int64_t)n * A.stride;
-    int q = (OP == OP_FWD) ? n : mk_pos(n, N);
-    TC v = res[c * ls + q] * A.outscale;
-    if (ST == ST_ACCUM) {
-      reinterpret_cast<double*>(A.out)[p] = A.rphi[p] + (double)v;
-    } else {
-      out[p] = (TO)v;
-    }
-  }
+  gen_store<TC, TO, ST>(A, G, tid, nthr, [&](int c, int n) {
+    return res[c * ls + (OP == OP_FWD ? n : mk_pos(n, N))] * A.outscale;
+  });
 }
 
 // DCT-I of the lines of a vertex axis (n points, mirror about the end
@@ -341,8 +473,8 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
 // X_k = Re(E_k + w^k O_k), w = exp(-2 pi i / NS), X_H = E_0 - O_0 (the
 // spectrum of an even sequence is real); the inverse builds Z from the real
 // spectrum with the same split, runs the inverse FFT and scales by 1/H.
-// C lines per workgroup in three LDS regions (two FFT buffers and the
-// spectra); lines past the end of a partial tile are masked.
+// C lines per workgroup in two LDS buffers; lines past the end of a partial
+// tile are masked.
 template <typename TC, typename TI, typename TO, int OP, int LD, int ST>
 __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -352,49 +484,37 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   const int lsc = ls >> 1;
   TC* s0 = reinterpret_cast<TC*>(smem_raw);
   TC* s1 = s0 + (size_t)C * ls;
-  TC* xs = s1 + (size_t)C * ls;
+  cplx<TC>* twl = reinterpret_cast<cplx<TC>*>(s1 + (size_t)C * ls);
+  // the spectrum, and the inverse FFT's input: after a forward FFT the buffer
+  // that does not hold its result and the one that does
+  TC* xs = s1;
+  TC* zs = s0;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int t = A.axis == 0 ? blockIdx.x : xcd_tile(blockIdx.x, gridDim.x);
   const TI* __restrict__ in = reinterpret_cast<const TI*>(A.in);
-  TO* __restrict__ out = reinterpret_cast<TO*>(A.out);
   const AxisTables<TC>& Tb = A.tab;
-  // global index of point i of line c (or -1 past the end of the tile)
-  auto gidx = [&](int c, int i) -> int64_t {
-    int li, lo;
-    const int64_t b = line_base(A, t, c, &li, &lo);
-    if (A.axis == 0 ? (int64_t)t * C + c >= A.lines : li >= A.n0) return -1;
-    return b + (int64_t)i * A.stride;
-  };
-  // element e of the tile's points: line c, point i (rows: points of a line
-  // adjacent; strided: lines adjacent)
-  auto split_e = [&](int e, int* c, int* i) {
-    if (A.axis == 0) { *c = e / n; *i = e - *c * n; } else { *i = e / C; *c = e - *i * C; }
-  };
+  const GenTile G = gen_tile(A, t);
+  const double sub = A.sub ? *A.sub : 0.0;
+  if (A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
 
   if (OP != OP_INV) {
-    for (int e = tid; e < C * n; e += nthr) {
-      int c, i;
-      split_e(e, &c, &i);
-      const int64_t p = gidx(c, i);
-      TC v = TC(0);
-      if (p >= 0) {
-        if (LD == LD_RESID) {
-          double r = resid_at<true>(A.rb, A.rphi, p, A.d, A.n0, A.n1, A.n2, A.perm, A.ih2, A.rscale);
-          if (A.sub) r -= *A.sub;
-          v = (TC)r;
-        } else if (A.sub) {
-          v = (TC)((double)in[p] - *A.sub);
-        } else {
-          v = (TC)in[p];
-        }
-      }
-      s0[c * ls + i] = v;
-      if (i > 0 && i < n - 1) s0[c * ls + NS - i] = v;
-    }
+    batched<LD == LD_RESID ? 2 : 4, TC>(
+        C * n, tid, nthr,
+        [&](int e) { return gen_load<TC, TI, LD, true>(A, G, in, sub, e); },
+        [&](int e, TC v) {
+          int c, i;
+          G.split(e, &c, &i);
+          s0[c * ls + i] = v;
+          if (i > 0 && i < n - 1) s0[c * ls + NS - i] = v;
+        });
     __syncthreads();
     const cplx<TC>* zf = fft_lds_mixed<TC, false>(reinterpret_cast<cplx<TC>*>(s0),
-                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A,
+                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
                                                   tid, nthr);
+    if (reinterpret_cast<const TC*>(zf) != s0) {
+      xs = s0;
+      zs = s1;
+    }
     for (int e = tid; e < C * n; e += nthr) {
       const int c = e / n, k = e - c * n;
       const cplx<TC>* z = zf + c * lsc;
@@ -415,24 +535,18 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
     }
     __syncthreads();
     if (OP == OP_FWD) {
-      for (int e = tid; e < C * n; e += nthr) {
-        int c, i;
-        split_e(e, &c, &i);
-        const int64_t p = gidx(c, i);
-        if (p >= 0) out[p] = (TO)(xs[c * ls + i] * A.outscale);
-      }
+      gen_store<TC, TO, ST_PLAIN>(A, G, tid, nthr,
+                                  [&](int c, int i) { return xs[c * ls + i] * A.outscale; });
       return;
     }
     // FDI: divide by the summed eigenvalues (slot k of this axis)
     for (int e = tid; e < C * n; e += nthr) {
       const int c = e / n, k = e - c * n;
-      int li, lo;
-      (void)line_base(A, t, c, &li, &lo);
-      const bool valid = A.axis == 0 ? (int64_t)t * C + c < A.lines : li < A.n0;
+      const bool valid = c < G.nval;
       TC rest = TC(0);
       if (valid) {
-        rest = A.lam0[li];
-        if (A.lam1) rest += A.lam1[lo];
+        rest = A.lam0[G.i0 + c];
+        if (A.lam1) rest += A.lam1[G.o0];
       }
       const TC l = (rest + Tb.lam[k]) * A.lscale;
       const TC X = xs[c * ls + k];
@@ -441,16 +555,18 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
     }
     __syncthreads();
   } else {
-    for (int e = tid; e < C * n; e += nthr) {
-      int c, i;
-      split_e(e, &c, &i);
-      const int64_t p = gidx(c, i);
-      xs[c * ls + i] = p >= 0 ? (TC)in[p] : TC(0);
-    }
+    batched<4, TC>(
+        C * n, tid, nthr,
+        [&](int e) { return gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e); },
+        [&](int e, TC v) {
+          int c, i;
+          G.split(e, &c, &i);
+          xs[c * ls + i] = v;
+        });
     __syncthreads();
   }
   // inverse: Z[k] from the real spectrum (imaginary parts zero)
-  cplx<TC>* za = reinterpret_cast<cplx<TC>*>(s0);
+  cplx<TC>* za = reinterpret_cast<cplx<TC>*>(zs);
   for (int e = tid; e < C * H; e += nthr) {
     const int c = e / H, k = e - c * H;
     const TC xk = xs[c * ls + k], xhk = xs[c * ls + H - k];
@@ -458,18 +574,9 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   }
   __syncthreads();
   const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, tid, nthr));
-  for (int e = tid; e < C * n; e += nthr) {
-    int c, i;
-    split_e(e, &c, &i);
-    const int64_t p = gidx(c, i);
-    if (p < 0) continue;
-    const TC v = er[c * ls + i] * A.outscale;
-    if (ST == ST_ACCUM)
-      reinterpret_cast<double*>(A.out)[p] = A.rphi[p] + (double)v;
-    else
-      out[p] = (TO)v;
-  }
+      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+  gen_store<TC, TO, ST>(A, G, tid, nthr,
+                        [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
 
 // The packed real DFT of the lines of a periodic axis of any even length N
@@ -477,8 +584,8 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
 // slot k = Re X_k, slot N-k = Im X_k, slot H = X_H): the half-length complex
 // FFT of z[m] = x[2m] + i x[2m+1] (mixed radix, H = N/2) and the real-FFT
 // split X_k = E_k + w^k O_k, w = exp(-2 pi i / N); the inverse runs the same
-// steps backwards and scales by 1/H.  C lines per workgroup in three LDS
-// regions; lines past the end of a partial tile are masked.
+// steps backwards and scales by 1/H.  C lines per workgroup in two LDS
+// buffers; lines past the end of a partial tile are masked.
 template <typename TC, typename TI, typename TO, int OP, int LD, int ST>
 __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -488,46 +595,37 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   const int lsc = ls >> 1;
   TC* s0 = reinterpret_cast<TC*>(smem_raw);
   TC* s1 = s0 + (size_t)C * ls;
-  TC* xs = s1 + (size_t)C * ls;
+  cplx<TC>* twl = reinterpret_cast<cplx<TC>*>(s1 + (size_t)C * ls);
+  // the spectrum, and the inverse FFT's input: after a forward FFT the buffer
+  // that does not hold its result and the one that does
+  TC* xs = s1;
+  TC* zs = s0;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int t = A.tiles ? A.tiles[blockIdx.x]
                         : (A.axis == 0 ? blockIdx.x : xcd_tile(blockIdx.x, gridDim.x));
   const TI* __restrict__ in = reinterpret_cast<const TI*>(A.in);
-  TO* __restrict__ out = reinterpret_cast<TO*>(A.out);
   const AxisTables<TC>& Tb = A.tab;
-  auto gidx = [&](int c, int i) -> int64_t {
-    int li, lo;
-    const int64_t b = line_base(A, t, c, &li, &lo);
-    if (A.axis == 0 ? (int64_t)t * C + c >= A.lines : li >= A.n0) return -1;
-    return b + (int64_t)i * A.stride;
-  };
-  auto split_e = [&](int e, int* c, int* i) {
-    if (A.axis == 0) { *c = e / N; *i = e - *c * N; } else { *i = e / C; *c = e - *i * C; }
-  };
+  const GenTile G = gen_tile(A, t);
+  const double sub = A.sub ? *A.sub : 0.0;
+  if (A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
 
   if (OP != OP_INV) {
-    for (int e = tid; e < C * N; e += nthr) {
-      int c, i;
-      split_e(e, &c, &i);
-      const int64_t p = gidx(c, i);
-      TC v = TC(0);
-      if (p >= 0) {
-        if (LD == LD_RESID) {
-          double r = resid_at(A.rb, A.rphi, p, A.d, A.n0, A.n1, A.n2, A.perm, A.ih2, A.rscale);
-          if (A.sub) r -= *A.sub;
-          v = (TC)r;
-        } else if (A.sub) {
-          v = (TC)((double)in[p] - *A.sub);
-        } else {
-          v = (TC)in[p];
-        }
-      }
-      s0[c * ls + i] = v;
-    }
+    batched<LD == LD_RESID ? 2 : 4, TC>(
+        C * N, tid, nthr,
+        [&](int e) { return gen_load<TC, TI, LD, false>(A, G, in, sub, e); },
+        [&](int e, TC v) {
+          int c, i;
+          G.split(e, &c, &i);
+          s0[c * ls + i] = v;
+        });
     __syncthreads();
     const cplx<TC>* zf = fft_lds_mixed<TC, false>(reinterpret_cast<cplx<TC>*>(s0),
-                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A,
+                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
                                                   tid, nthr);
+    if (reinterpret_cast<const TC*>(zf) != s0) {
+      xs = s0;
+      zs = s1;
+    }
     // split: slots k and N-k from the own index k (k < H), slot H from k = 0
     for (int e = tid; e < C * H; e += nthr) {
       const int c = e / H, k = e - c * H;
@@ -546,23 +644,17 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
     }
     __syncthreads();
     if (OP == OP_FWD) {
-      for (int e = tid; e < C * N; e += nthr) {
-        int c, i;
-        split_e(e, &c, &i);
-        const int64_t p = gidx(c, i);
-        if (p >= 0) out[p] = (TO)(xs[c * ls + i] * A.outscale);
-      }
+      gen_store<TC, TO, ST_PLAIN>(A, G, tid, nthr,
+                                  [&](int c, int i) { return xs[c * ls + i] * A.outscale; });
       return;
     }
     for (int e = tid; e < C * N; e += nthr) {
       const int c = e / N, k = e - c * N;
-      int li, lo;
-      (void)line_base(A, t, c, &li, &lo);
-      const bool valid = A.axis == 0 ? (int64_t)t * C + c < A.lines : li < A.n0;
+      const bool valid = c < G.nval;
       TC rest = TC(0);
       if (valid) {
-        rest = A.lam0[li];
-        if (A.lam1) rest += A.lam1[lo];
+        rest = A.lam0[G.i0 + c];
+        if (A.lam1) rest += A.lam1[G.o0];
       }
       const TC l = (rest + Tb.lam[k]) * A.lscale;  // the table is by slot
       const TC X = xs[c * ls + k];
@@ -571,15 +663,17 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
     }
     __syncthreads();
   } else {
-    for (int e = tid; e < C * N; e += nthr) {
-      int c, i;
-      split_e(e, &c, &i);
-      const int64_t p = gidx(c, i);
-      xs[c * ls + i] = p >= 0 ? (TC)in[p] : TC(0);
-    }
+    batched<4, TC>(
+        C * N, tid, nthr,
+        [&](int e) { return gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e); },
+        [&](int e, TC v) {
+          int c, i;
+          G.split(e, &c, &i);
+          xs[c * ls + i] = v;
+        });
     __syncthreads();
   }
-  cplx<TC>* za = reinterpret_cast<cplx<TC>*>(s0);
+  cplx<TC>* za = reinterpret_cast<cplx<TC>*>(zs);
   for (int e = tid; e < C * H; e += nthr) {
     const int c = e / H, k = e - c * H;
     const TC* x = xs + c * ls;
@@ -589,18 +683,9 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   }
   __syncthreads();
   const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, tid, nthr));
-  for (int e = tid; e < C * N; e += nthr) {
-    int c, i;
-    split_e(e, &c, &i);
-    const int64_t p = gidx(c, i);
-    if (p < 0) continue;
-    const TC v = er[c * ls + i] * A.outscale;
-    if (ST == ST_ACCUM)
-      reinterpret_cast<double*>(A.out)[p] = A.rphi[p] + (double)v;
-    else
-      out[p] = (TO)v;
-  }
+      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+  gen_store<TC, TO, ST>(A, G, tid, nthr,
+                        [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
 
 // ---- deterministic mean ----------------------------------------------------
@@ -755,11 +840,11 @@ void tile_shape(int axis, int N, int lines_x, int64_t groups, int* C, int* nthr,
     while (c > 1 && (size_t)c * N * sizeof(TC) * 2 > (size_t)lim / 2) c >>= 1;
   }
   while (c > 1 && (c > lines_x || lines_x % c)) c >>= 1;
-  while (c > 1 && (size_t)c * N * sizeof(TC) * 2 > (size_t)lim) c >>= 1;
+  while (c > 1 && (size_t)c * N * sizeof(TC) * 2 + LTW_MAX > (size_t)lim) c >>= 1;
   c = fill_device(c, (int64_t)(lines_x / c) * groups);
-  int want = c * H / 4;
-  if (want < 64) want = 64;
-  int t = want > 1024 ? 1024 : want;
+  // one thread per four complex values (small tiles: two wavefronts at least,
+  // so that their memory latencies overlap); B bounds the pairs per thread
+  const int t = std::min(1024, (std::max(128, c * H / 4) + 63) / 64 * 64);
   int b = (c * H / 4 + t - 1) / t;
   if (b < 1) b = 1;
   *C = c;
@@ -786,6 +871,17 @@ int generic_radices(int H, int* rad) {
     }
   }
   return H == 1 ? n : -1;
+}
+
+// Whether a pass keeps its half-length twiddles in LDS as well: for the direct
+// sums of a prime factor of 11 or more, which read one per term (402^2 sub-step
+// 557 us against 637, 190 x 184 x 176 float32 solve 295 against 353); not on
+// lines above 512 points, where the LDS is worth more as occupancy (1998 x
+// 1540 solve 240 us against 366).
+bool lds_twiddles(int N, const int* rad, int nrad) {
+  for (int i = 0; i < nrad; ++i)
+    if (rad[i] >= 11) return N <= 512;
+  return false;
 }
 
 bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
@@ -853,8 +949,8 @@ static int generic_tile_lines(const pc_plan* P, int axis, size_t elem, int* nthr
   const int64_t lines = P->G / N;
   int C = 1, t = 64, b = 1;
   if (P->bc[axis] == PC_BC_PERIODIC) {
-    const size_t per_line = (size_t)3 * (N + 2) * elem;
-    const int cmax = (int)std::max<size_t>(1, (size_t)lds_limit() / per_line);
+    const size_t per_line = (size_t)2 * (N + 2) * elem;
+    const int cmax = (int)std::max<size_t>(1, ((size_t)lds_limit() - LTW_MAX) / per_line);
     const int want = axis == 0 ? std::max(1, 2048 / N) : (int)(128 / elem);
     while (2 * C <= std::min(want, cmax)) C <<= 1;
     C = fill_device(C, axis == 0 ? (lines + C - 1) / C
@@ -946,21 +1042,23 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
   int64_t lines = P->G / A.N;
   A.lines = lines;
   if (P->vertex) {
-    // DCT-I kernel: C lines of the even extension (NS reals) in three LDS
-    // regions; partial tiles are masked, so C need not divide the counts
+    // DCT-I kernel: C lines of the even extension (NS reals) in two LDS
+    // buffers; partial tiles are masked, so C need not divide the counts
     const int Hv = A.N - 1, NS = 2 * Hv;
     A.nrad = generic_radices(Hv, A.rad);
     if (A.nrad < 0) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform length has too many factors");
     A.outscale = (OP == OP_FWD) ? TC(1) : TC(1.0 / (double)Hv);
     A.pad = 2;
-    const size_t per_line = (size_t)3 * (NS + A.pad) * sizeof(TC);
-    const int cmax = (int)std::max<size_t>(1, (size_t)lds_limit() / per_line);
+    const size_t per_line = (size_t)2 * (NS + A.pad) * sizeof(TC);
+    A.ltw = lds_twiddles(NS, A.rad, A.nrad);
+    const size_t tw = A.ltw ? (size_t)NS * sizeof(TC) : 0;  // the twiddles' LDS copy
+    const int cmax = (int)std::max<size_t>(1, ((size_t)lds_limit() - tw) / per_line);
     int C = 1;
     const int want = axis == 0 ? std::max(1, 2048 / NS) : (int)(128 / sizeof(TC));
     while (2 * C <= std::min(want, cmax)) C <<= 1;
     C = fill_device(C, axis == 0 ? (lines + C - 1) / C
                                  : (int64_t)((P->n[0] + C - 1) / C) * (lines / P->n[0]));
-    if ((size_t)C * per_line > (size_t)lds_limit())
+    if ((size_t)C * per_line + tw > (size_t)lds_limit())
       return fail(PC_ERR_UNSUPPORTED_SIZE, "transform line does not fit in LDS");
     if ((int64_t)C * NS >= (1 << 17))  // div_small's range (butterfly indices)
       return fail(PC_ERR_UNSUPPORTED_SIZE, "transform tile too large");
@@ -972,9 +1070,9 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
       A.tx = (P->n[0] + C - 1) / C;
       ntile = (int64_t)A.tx * (lines / P->n[0]);
     }
-    int nthr = std::min(1024, std::max(64, C * Hv / 2));
+    int nthr = std::min(1024, std::max(128, C * Hv / 2));
     nthr = (nthr + 63) / 64 * 64;
-    const size_t lds = (size_t)C * per_line;
+    const size_t lds = (size_t)C * per_line + tw;
     const void* fn = (const void*)dct1_lines<TC, TI, TO, OP, LD, ST>;
     if (lds > 65536)
       PC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1017,9 +1115,11 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     A.nrad = generic_radices(H, A.rad);
     if (A.nrad < 0) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform length has too many factors");
     A.pad = 2;
-    const size_t per_line = (size_t)3 * (A.N + A.pad) * sizeof(TC);
+    const size_t per_line = (size_t)2 * (A.N + A.pad) * sizeof(TC);
+    A.ltw = lds_twiddles(A.N, A.rad, A.nrad);
+    const size_t tw = A.ltw ? (size_t)A.N * sizeof(TC) : 0;  // the twiddles' LDS copy
     const int C = generic_tile_lines(P, axis, sizeof(TC), nullptr, nullptr);
-    if ((size_t)C * per_line > (size_t)lds_limit())
+    if ((size_t)C * per_line + tw > (size_t)lds_limit())
       return fail(PC_ERR_UNSUPPORTED_SIZE, "transform line does not fit in LDS");
     if ((int64_t)C * A.N >= (1 << 17))  // div_small's range (butterfly indices)
       return fail(PC_ERR_UNSUPPORTED_SIZE, "transform tile too large");
@@ -1035,9 +1135,9 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
       if (ntiles <= 0) return PC_OK;
       ntile = ntiles;
     }
-    int nthr = std::min(1024, std::max(64, C * H / 2));
+    int nthr = std::min(1024, std::max(128, C * H / 2));
     nthr = (nthr + 63) / 64 * 64;
-    const size_t lds = (size_t)C * per_line;
+    const size_t lds = (size_t)C * per_line + tw;
     const void* fn = (const void*)rdft_lines<TC, TI, TO, OP, LD, ST>;
     if (lds > 65536)
       PC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1067,8 +1167,10 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     ntile = ntiles;
   }
   // pad each LDS line by one complex when it fits (fewer bank conflicts)
-  A.pad = ((size_t)C * (A.N + 2) * sizeof(TC) * 2 <= (size_t)lds_limit()) ? 2 : 0;
-  size_t lds = (size_t)C * (A.N + A.pad) * sizeof(TC) * 2;
+  A.ltw = lds_twiddles(A.N, A.rad, A.nrad);
+  const size_t tw = A.ltw ? (size_t)A.N * sizeof(TC) : 0;  // the twiddles' LDS copy
+  A.pad = ((size_t)C * (A.N + 2) * sizeof(TC) * 2 + tw <= (size_t)lds_limit()) ? 2 : 0;
+  size_t lds = (size_t)C * (A.N + A.pad) * sizeof(TC) * 2 + tw;
   if (lds > (size_t)lds_limit()) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform line too long");
   dim3 grid(ntile), block(nthr);
   const void* fn;

@@ -55,6 +55,7 @@ struct LineArgs {
   int N, logH;
   int nrad;             // generic kernel: the radices of the half length H
   int rad[24];
+  int ltw;              // generic kernels: the twiddles are copied to LDS
   int pad;              // LDS line padding in reals (0 or 2)
   int C;                // lines per tile
   int tx;               // tiles along x (strided axes)
@@ -301,6 +302,42 @@ __device__ __forceinline__ void dft5(cplx<TC>* v) {
   v[4] = csub(a1, ib1);
   v[2] = cadd(a2, ib2);
   v[3] = csub(a2, ib2);
+}
+
+// DFT of length 7 from the sums and differences of the inputs j and 7 - j:
+// X[k], X[7-k] = v_0 + sum_j cos(2 pi j k / 7) (v_j + v_{7-j})
+//                -+ i sum_j sin(2 pi j k / 7) (v_j - v_{7-j}).
+template <typename TC, bool INV>
+__device__ __forceinline__ void dft7(cplx<TC>* v) {
+  constexpr double C[3] = {0.62348980185873353053, -0.22252093395631440429,
+                           -0.90096886790241912624};  // cos(2 pi j / 7)
+  constexpr double S[3] = {0.78183148246802980871, 0.97492791218182360702,
+                           0.43388373911755812048};   // sin(2 pi j / 7)
+  cplx<TC> t[3], d[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    t[j] = cadd(v[j + 1], v[6 - j]);
+    d[j] = csub(v[j + 1], v[6 - j]);
+  }
+  const cplx<TC> v0 = v[0];
+  v[0] = cadd(v0, cadd(t[0], cadd(t[1], t[2])));
+#pragma unroll
+  for (int k = 1; k <= 3; ++k) {
+    cplx<TC> a = v0, b = {TC(0), TC(0)};
+#pragma unroll
+    for (int j = 1; j <= 3; ++j) {
+      const int m = (j * k) % 7;
+      const TC c = (TC)C[(m <= 3 ? m : 7 - m) - 1];
+      const TC sn = (TC)((m <= 3 ? 1.0 : -1.0) * S[(m <= 3 ? m : 7 - m) - 1]);
+      a.re += c * t[j - 1].re;
+      a.im += c * t[j - 1].im;
+      b.re += sn * d[j - 1].re;
+      b.im += sn * d[j - 1].im;
+    }
+    const cplx<TC> ib = INV ? cplx<TC>{-b.im, b.re} : cplx<TC>{b.im, -b.re};  // -+ i b
+    v[k] = cadd(a, ib);
+    v[7 - k] = csub(a, ib);
+  }
 }
 
 // DFT of length 10 (natural order in and out) as two of length 5: E and O
