@@ -247,8 +247,9 @@ int ensure_plan_ws(const pc_plan* P, pc_workspace** ws);
 // Complex values per thread of the register transform of an axis of N
 // points: 8 (radix-8 plan, N a power of two from 32 to 4096) or 4 (radix-4
 // plan, N up to 2048), 10 (radix-10 plan, N = 200, 400, 1000 or 2000), 0 (the
-// generic kernel).
-int rad_values(const pc_plan* P, int axis);
+// generic kernel); the choice depends on the plan and on
+// the size of the transform's elements alone.
+int rad_values(const pc_plan* P, int axis, size_t elem);
 // Lines per workgroup tile of the register transform along `axis` for
 // elements of `elem` bytes (0 when the axis uses the generic kernel).
 int rad_tile_lines(const pc_plan* P, int axis, size_t elem);

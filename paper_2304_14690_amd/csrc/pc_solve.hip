@@ -108,8 +108,14 @@ __device__ __forceinline__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int
       case 3: stage(std::integral_constant<int, 3>{}); break;
       case 4: stage(std::integral_constant<int, 4>{}); break;
       case 5: stage(std::integral_constant<int, 5>{}); break;
-      case 7: stage(std::integral_constant<int, 7>{}); break;
       case 8: stage(std::integral_constant<int, 8>{}); break;
+      case 7:
+        // (float32 lines above 512 points keep the direct sum: float_noise)
+        if (sizeof(TC) == 8 || H <= 256) {
+          stage(std::integral_constant<int, 7>{});
+          break;
+        }
+        [[fallthrough]];
       default: {
         // a direct sum per output: output s' of butterfly g takes
         // v_s W_r^(s s') with W_r^m = twH[nb (m mod r)]; a thread per output,
@@ -886,6 +892,15 @@ bool lds_twiddles(int N, const int* rad, int nrad) {
 
 bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
+// 2D grids with more than 512 points along an axis, in float32: the velocity's
+// own rounding noise, that of the float32 pressure over a spacing, reaches
+// 1e-5 to 3e-5 there, and a plan with another rounding would move results by as
+// much (1024^2: 1.8e-5, 2048^2: 2.8e-5).  Their axes keep the radix-8 and
+// radix-10 plans (and 7 its direct sum), worth 2% (1024^2) and 5% (2048^2).
+static bool float_noise(const pc_plan* P, size_t elem) {
+  return elem == 4 && P->d == 2 && std::max(P->n[0], P->n[1]) > 512;
+}
+
 // Radix 4 where a pass is bound by a wavefront's own instructions and latency
 // rather than by the device: on every axis of grids of up to 2^20 points, which
 // leave the radix-8 plan at most one wavefront per SIMD (N up to 1024 on the
@@ -897,12 +912,18 @@ bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 // Sub-steps, radix 8 -> this rule: 64^2 240 -> 223 us, 512^2 231 -> 216,
 // 1024^2 311 -> 305, 2048^2 617 -> 587, 64^3 280 -> 260, 128^3 544 -> 514
 // (mixed 897 -> 844), 256^3 2.75 -> 2.71 ms.
-int rad_values(const pc_plan* P, int axis) {
+int rad_values(const pc_plan* P, int axis, size_t elem) {
   const int N = P->n[axis];
-  const bool small = P->G <= (int64_t)1 << 20;
+  const bool small = P->G <= (int64_t)1 << 20 && !float_noise(P, elem);
   const int lim4 = axis == 0 ? 2048 : (axis < P->d - 1 ? (small ? 512 : 256) : (small ? 1024 : 0));
-  if (N >= 32 && N <= lim4 && pow2(N)) return 4;
+  if (N >= 32 && N <= lim4 && pow2(N) && !float_noise(P, elem)) return 4;
   if (N >= 32 && N <= 4096 && pow2(N)) return 8;
+  // The radix-10 plan's 20 threads a line of 400 points leave the fused last
+  // axis of a small grid at 17.4 us where the generic kernel, with a thread
+  // per two points, takes 13.6 (400^2 periodic sub-step 389 -> 356 us, 200^2
+  // 260 -> 247); a Neumann axis of 400 is equal (13.0 us), longer ones slower.
+  if (small && axis == P->d - 1 && (N == 200 || (N == 400 && P->bc[axis] == PC_BC_PERIODIC)))
+    return 0;
   if (N == 200 || N == 400 || N == 1000 || N == 2000) return 10;
   return 0;
 }
@@ -920,7 +941,7 @@ int floor_pow2(int v) {
 // the axis uses the generic kernel: N < 32 or not a power of two).
 int rad_tile_lines(const pc_plan* P, int axis, size_t elem) {
   const int N = P->n[axis];
-  const int RT = rad_values(P, axis);
+  const int RT = rad_values(P, axis, elem);
   if (!RT) return 0;
   const int H = N / 2, T = H / RT, LS = H + H / 16 + 1;
   const int64_t lines = P->G / N;
@@ -975,7 +996,7 @@ PassTiles pass_tiles(const pc_plan* P, int axis, size_t elem) {
   PassTiles pt{};
   const int N = P->n[axis];
   const int64_t lines = P->G / N;
-  const bool reg = rad_values(P, axis) != 0;
+  const bool reg = rad_values(P, axis, elem) != 0;
   const bool masked = !reg && P->bc[axis] == PC_BC_PERIODIC;
   pt.C = reg ? rad_tile_lines(P, axis, elem) : generic_tile_lines(P, axis, elem, nullptr, nullptr);
   if (axis == 0) {
@@ -1081,7 +1102,7 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     PC_HIP_CHECK(hipGetLastError());
     return PC_OK;
   }
-  if (const int RT = rad_values(P, axis)) {
+  if (const int RT = rad_values(P, axis, sizeof(TC))) {
     // register kernel: T = H/RT threads per line, C lines per group
     const int T = H / RT;
     const int LS = H + H / 16 + 1;

@@ -1,4 +1,4 @@
-"""The register transforms on both sides of the radix-4 / radix-8 rule: the
+"""The register transforms on both sides of the rules that choose their plan: the
 fused last axis and the middle axis of grids of 2^20 points (radix 4) and
 above (radix 8), and long x rows, as cosine and real Fourier transforms in
 every precision, against the oracle's solve (the bars of the solves: float64
@@ -17,6 +17,9 @@ CASES = [
     ((4096, 258), (NE, NE)), ((1024, 1026), (P, NE)),
     ((64, 512, 32), (NE, P, NE)), ((128, 512, 32), (P, NE, P)), ((512, 256, 64), (NE, NE, P)),
     ((64, 64, 512), (P, P, NE)), ((256, 32, 32), (P, P, P)),
+    # radix 10: last axes of 200 and 400 points on both sides of their rule
+    ((4096, 400), (NE, P)), ((64, 128, 200), (P, NE, P)), ((64, 128, 200), (NE, P, NE)),
+    ((400, 400), (P, P)), ((200, 200), (NE, NE)), ((200, 200), (P, P)),
 ]
 
 
@@ -26,7 +29,7 @@ def pc():
     return pcorr
 
 
-@pytest.mark.parametrize("n,bc", CASES, ids=["x".join(map(str, n)) for n, _ in CASES])
+@pytest.mark.parametrize("n,bc", CASES, ids=["x".join(map(str, n)) + "-" + "".join(c[0] for c in bc) for n, bc in CASES])
 def test_solve_on_both_sides_of_the_rule(pc, n, bc):
     import torch
     d = len(n)
