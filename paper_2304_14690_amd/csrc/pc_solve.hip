@@ -909,13 +909,20 @@ static bool float_noise(const pc_plan* P, size_t elem) {
 // last axis of larger grids is faster with radix 8 (256^3: 88 against 105 us),
 // and so is a middle axis above 256 points, whose tiles would shrink below
 // 64 bytes of adjacent lines (512^3 float32 solve: 1.19 against 1.30 ms).
-// Sub-steps, radix 8 -> this rule: 64^2 240 -> 223 us, 512^2 231 -> 216,
+// Float32 grids above 2^24 points and more than 2048 x rows of a large 2D grid
+// are bound by the device again and take radix 8 (solves, radix 4 -> 8:
+// 512 x 256 x 256 float32 286 -> 271 us, 256 x 256 x 512 285 -> 272, 1024 x 4096
+// float64 71 -> 68; on the other side 256^3 float32 152 -> 150 and 2048^2 66 -> 64.5
+// by radix 4).  Sub-steps, radix 8 -> radix 4: 64^2 240 -> 223 us, 512^2 231 -> 216,
 // 1024^2 311 -> 305, 2048^2 617 -> 587, 64^3 280 -> 260, 128^3 544 -> 514
 // (mixed 897 -> 844), 256^3 2.75 -> 2.71 ms.
 int rad_values(const pc_plan* P, int axis, size_t elem) {
   const int N = P->n[axis];
   const bool small = P->G <= (int64_t)1 << 20 && !float_noise(P, elem);
-  const int lim4 = axis == 0 ? 2048 : (axis < P->d - 1 ? (small ? 512 : 256) : (small ? 1024 : 0));
+  const bool bulk = (elem == 4 && P->G > (int64_t)1 << 24) ||
+                    (axis == 0 && P->d == 2 && !small && P->G / N > 2048);
+  const int lim4 = bulk ? 0 : axis == 0 ? 2048
+                   : (axis < P->d - 1 ? (small ? 512 : 256) : (small ? 1024 : 0));
   if (N >= 32 && N <= lim4 && pow2(N) && !float_noise(P, elem)) return 4;
   if (N >= 32 && N <= 4096 && pow2(N)) return 8;
   // The radix-10 plan's 20 threads a line of 400 points leave the fused last

@@ -17,6 +17,8 @@ CASES = [
     ((4096, 258), (NE, NE)), ((1024, 1026), (P, NE)),
     ((64, 512, 32), (NE, P, NE)), ((128, 512, 32), (P, NE, P)), ((512, 256, 64), (NE, NE, P)),
     ((64, 64, 512), (P, P, NE)), ((256, 32, 32), (P, P, P)),
+    # more than 2048 x rows of a large 2D grid, 3D grids above 2^24 points
+    ((1024, 4096), (NE, P)), ((512, 2048), (P, NE)), ((512, 512, 128), (NE, NE, P)),
     # radix 10: last axes of 200 and 400 points on both sides of their rule
     ((4096, 400), (NE, P)), ((64, 128, 200), (P, NE, P)), ((64, 128, 200), (NE, P, NE)),
     ((400, 400), (P, P)), ((200, 200), (NE, NE)), ((200, 200), (P, P)),
