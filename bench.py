@@ -136,8 +136,16 @@ def parse():
 
 # ---- algorithmic bytes ---------------------------------------------------------
 def bytes_div_all(G, M, k, d, s):
-    """idx (4 B) + d coefficients per stencil entry, b written once, u read once."""
+    """Stored coefficients: idx (4 B) + d coefficients per stencil entry, b
+    written once, u read once."""
     return G * (k * (4 + d * s) + s) + M * d * s
+
+
+def bytes_div_rows(G, M, k, d, s):
+    """Coefficients evaluated from rows: 12 (2D) or 28 (3D) float64 of rows and
+    a 16-bit place per stencil entry (two to a word), b written once, the
+    nodes' positions (float64), values and list entry once."""
+    return G * ((12 if d == 2 else 28) * 8 + (k + 1) // 2 * 4 + s) + M * (d * 8 + d * s + 4)
 
 
 def bytes_solve_pass(G, s_in, s_out):
@@ -149,13 +157,21 @@ def bytes_solve(G, d, s):
 
 
 def bytes_grad(G, M, bn, d, s):
-    """coefficients + block corner per node, phi read once, gradient written."""
+    """Stored rows: coefficients + block corner per node, phi read once,
+    gradient written."""
     return M * (bn * d * s + 4 + d * s) + G * s
 
 
 def bytes_grad_project(G, M, bn, d, s):
-    """coefficients + block corner per node, u* read, u^{n+1} written, phi read once."""
+    """Stored rows: coefficients + block corner per node, u* read, u^{n+1}
+    written, phi read once."""
     return M * (bn * d * s + 4 + 2 * d * s) + G * s
+
+
+def bytes_grad_fit(G, M, d, s, project=False):
+    """Rows from positions: the position (float64) and block corner per node,
+    phi read once, the gradient written (project: u* read, u^{n+1} written)."""
+    return M * (d * 8 + 4 + (2 if project else 1) * d * s) + G * s
 
 
 def bytes_momentum(M, k, d, s):
@@ -231,7 +247,7 @@ def bytes_solve_mode(G, d, mode, sweeps, warm=False, near_lines=(0.0, 0.0)):
 
 
 def bytes_step(G, M, k, bn, d, mode, sweeps, n_it, n_near, near_entries, n_ib,
-               near_lines=(0.0, 0.0)):
+               near_lines=(0.0, 0.0), evaluated=False):
     """Algorithmic bytes of one sub-step: the RHS transfer at every grid
     point, n_it solves, the near-IB RHS update in every iteration after the
     first (the B+V entries of the near stencils, b_u read and b written at
@@ -239,18 +255,21 @@ def bytes_step(G, M, k, bn, d, mode, sweeps, n_it, n_near, near_entries, n_ib,
     change written), the IB step (gradient at the B+V nodes, force update)
     in every iteration, and the final gradient fused with the projection.
     The correction mode also takes mean(b_u) once and removes mean(phi) at
-    the end (8 + 24 bytes per grid point)."""
+    the end (8 + 24 bytes per grid point).  evaluated: the transfers' rows
+    are evaluated from positions (the workloads' geometries) instead of read
+    from stored coefficients."""
     s = 4 if mode == "f32" else 8
     near = near_entries * (4 + d * s) + n_near * (2 + (2 if mode == "mixed" else 0)) * s
-    ibstep = n_ib * (bn * d * s + 4 + 3 * d * s)
+    ibstep = n_ib * ((d * 8 if evaluated else bn * d * s) + 4 + 3 * d * s)
     solves = bytes_solve_mode(G, d, mode, sweeps)
     if mode == "mixed":
         solves += (n_it - 1) * bytes_solve_mode(G, d, mode, sweeps, True, near_lines)
         solves += 32 * G
     else:
         solves *= n_it
-    return (bytes_div_all(G, M, k, d, s) + bytes_grad_project(G, M, bn, d, s)
-            + solves + n_it * ibstep + (n_it - 1) * near)
+    transfers = (bytes_div_rows(G, M, k, d, s) + bytes_grad_fit(G, M, d, s, True) if evaluated
+                 else bytes_div_all(G, M, k, d, s) + bytes_grad_project(G, M, bn, d, s))
+    return (transfers + solves + n_it * ibstep + (n_it - 1) * near)
 
 
 def near_line_fractions(geom, n, d):
@@ -399,7 +418,7 @@ def run_workload(args, name, N, modes_arg):
         sec = total / args.steps
         nb = bytes_step(G, M, geom.k_grid, geom.bn, d, "mixed" if mname == "mixed3" else mname,
                         sweeps, stats["n_it"], geom.n_near, geom.near_entries, geom.n_ib,
-                        near_lines)
+                        near_lines, evaluated=True)
         results[mname] = {
             "value": G / sec,
             "ms_per_step": 1e3 * sec,
@@ -443,10 +462,8 @@ def run_workload(args, name, N, modes_arg):
 
     u64 = case["u"]
     # the outputs of these launches in one allocation, 256-byte aligned
-    # regions, as the sub-step's workspace holds b and phi: the large
-    # gathers' speed depends on where their output lands (k_div_all writing
-    # into a separate 1 GiB allocation at 512^3 takes 22.8 ms, into a region
-    # of a larger block 20.8 ms, inside the sub-step 20.9 ms)
+    # regions, as the sub-step's workspace holds b and phi: a large kernel's
+    # speed depends on where its output lands (up to 10% at 512^3)
     def aligned(n):
         return (n + 31) // 32 * 32
     blk = torch.empty(2 * aligned(G) + aligned(d * M), dtype=torch.float64, device="cuda")
@@ -465,13 +482,13 @@ def run_workload(args, name, N, modes_arg):
     # the solve call is 2d-1 kernels (forward passes, fused last-axis pass, inverse passes)
     kern = {
         "div_to_grid": {"kernel": f"k_div_all<double,{d},{k}>",
-                        "bytes": bytes_div_all(G, M, k, d, 8), "s": t_div,
+                        "bytes": bytes_div_rows(G, M, k, d, 8), "s": t_div,
                         "launches_per_step": 1, "kernels_per_call": 1},
         "poisson_fft_solve": {"kernel": f"dct_rad x{2 * d - 1}", "bytes": bytes_solve(G, d, 8),
                               "s": t_solve, "launches_per_step": n_it,
                               "kernels_per_call": 2 * d - 1},
-        "grad_to_nodes": {"kernel": f"k_grad_all<double,{d},{bn}>",
-                          "bytes": bytes_grad(G, M, bn, d, 8),
+        "grad_to_nodes": {"kernel": f"k_grad_fit<double,{d},{round(bn ** (1.0 / d))}>",
+                          "bytes": bytes_grad_fit(G, M, d, 8),
                           "s": t_grad, "launches_per_step": 1, "kernels_per_call": 1},
     }
     for v in kern.values():
