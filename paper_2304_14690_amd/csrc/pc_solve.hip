@@ -72,17 +72,23 @@ __device__ __forceinline__ void mixed_bfly(const cplx<TC>* x, cplx<TC>* y, int g
   for (int s = 0; s < R; ++s) y[s * L] = v[s];
 }
 
+// Whether lines of half length H take a factor of 7 as a direct sum too: float32
+// lines above 512 points, whose results a butterfly with another rounding would
+// move by up to their own rounding noise (the reason is at float_noise).
+__host__ __device__ constexpr bool sums7(int H, size_t elem) { return elem == 4 && H > 256; }
+
 // Mixed-radix Stockham FFT of the C lines held in LDS, for any H whose
 // factors are listed in A.rad (complex view, line c at a + c*lsc; b is a
 // second buffer of the same shape).  The stage of radix r after the stages
 // of combined length L takes butterfly g (k = g mod L) of each line:
 //   v_s = in[g + (H/r) s] w^(k s),  w = exp(-+2 pi i / (L r)),
 //   out[(g - k) r + k + s' L] = sum_{s<r} v_s exp(-+2 pi i s s' / r),
-// with w^e = twH[(H / (L r)) e]; radices 2, 3, 4, 5, 7 and 8 have their own butterflies, any other prime
-// factor (11, 67, ...) a direct sum of r terms per output, its twiddles from
-// the LDS copy twl where A.ltw says there is one.  Returns the buffer holding
-// the result (the stages alternate between a and b).
-template <typename TC, bool INV>
+// with w^e = twH[(H / (L r)) e]; radices 2, 3, 4, 5, 7 and 8 have their own
+// butterflies.  Any other prime factor (11, 67, ...) takes a direct sum of r
+// terms per output (SUM, direct_sums below), its twiddles from the LDS copy
+// twl where A.ltw says there is one.  Returns the buffer holding the result
+// (the stages alternate between a and b).
+template <typename TC, bool INV, bool SUM>
 __device__ __forceinline__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int lsc, int C, int H,
                                                    const LineArgs<TC>& A, const cplx<TC>* twl,
                                                    int tid, int nthr) {
@@ -110,13 +116,12 @@ __device__ __forceinline__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int
       case 5: stage(std::integral_constant<int, 5>{}); break;
       case 8: stage(std::integral_constant<int, 8>{}); break;
       case 7:
-        // (float32 lines above 512 points keep the direct sum: float_noise)
-        if (sizeof(TC) == 8 || H <= 256) {
+        if (!SUM || !sums7(H, sizeof(TC))) {
           stage(std::integral_constant<int, 7>{});
           break;
         }
         [[fallthrough]];
-      default: {
+      default: if constexpr (SUM) {
         // a direct sum per output: output s' of butterfly g takes
         // v_s W_r^(s s') with W_r^m = twH[nb (m mod r)]; a thread per output,
         // since a large prime leaves few butterflies (n/2 = 201: three)
@@ -154,14 +159,19 @@ __device__ __forceinline__ cplx<TC>* fft_lds_mixed(cplx<TC>* a, cplx<TC>* b, int
   return a;
 }
 
-// What bounds the generic kernels: on small grids the latency of each step (one
-// load at a time per thread, then a chain of table reads), on large ones LDS
-// and instruction issue.  Loads are batched, indices split without integer
-// division or 64-bit remainders, and a direct sum gives every output a thread
-// (one thread per butterfly left three threads busy on a 402-point line).
-// 402^2 float64 sub-step 12.3 ms -> 562 us, 280 x 480 350 -> 280 us, 150 x 136
-// x 84 1.37 -> 0.90 ms; solves 1998 x 1540 748 -> 247 us (float32 periodic 806
-// -> 230), 190 x 184 x 176 float32 965 -> 305, 1040 x 1404 periodic 214 -> 115.
+// What bounds the generic kernels: on small grids the latency of each step (a
+// chain of table reads), on large ones LDS and instruction issue.  Indices are
+// split without integer division or 64-bit remainders, and a direct sum gives
+// every output a thread (one thread per butterfly left three threads busy on a
+// 402-point line): 402^2 float64 solve 2042 -> 79 us, 1998 x 1540 748 -> 246,
+// 190 x 184 x 176 float32 966 -> 306, 280 x 480 (no direct sum) 42.5 -> 27.
+//   The direct sums are compiled into variants of their own (SUM): in one
+// kernel with the butterflies they made lengths that have none 5-15% slower
+// through its registers and schedule alone (solves, one kernel -> variants:
+// 192^3 periodic float32 281 -> 212 us, 160^3 208 -> 162, 512 x 256 x 192
+// 402 -> 324; 1025^2 vertex float32 90 -> 71; float64 Neumann 1536^2 99 -> 84,
+// 256 x 256 x 384 628 -> 569).  Loads and stores are plain loops: batches of 2 or
+// 4 loads a thread, and the same for stores, were 0.5-2% slower on 58 shapes.
 
 // The points of a generic kernel's tile: element e < C N is point n of line c
 // (rows: the points of a line adjacent, the C lines contiguous in memory;
@@ -219,28 +229,11 @@ __device__ __forceinline__ GenTile gen_tile(const LineArgs<TC>& A, int t) {
   return G;
 }
 
-// for e = tid, tid + nthr, ... < total: st(e, ld(e)), U loads before their
-// stores, so that a thread waits for memory once per U elements.
-template <int U, typename V, typename LDF, typename STF>
-__device__ __forceinline__ void batched(int total, int tid, int nthr, const LDF& ld,
-                                        const STF& st) {
-  for (int e0 = tid; e0 < total; e0 += U * nthr) {
-    V v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (e0 + u * nthr < total) v[u] = ld(e0 + u * nthr);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (e0 + u * nthr < total) st(e0 + u * nthr, v[u]);
-  }
-}
-
-// Point e of a tile as the forward transforms load it (0 outside the grid).
+// Element e of a tile, point n of line c, as the transforms load it (0 outside
+// the grid).
 template <typename TC, typename TI, int LD, bool VERTEX>
 __device__ __forceinline__ TC gen_load(const LineArgs<TC>& A, const GenTile& G, const TI* in,
-                                       double sub, int e) {
-  int c, n;
-  G.split(e, &c, &n);
+                                       double sub, int e, int c, int n) {
   if (c >= G.nval) return TC(0);
   const int64_t p = G.at(e, c, n);
   if (LD == LD_RESID) {
@@ -257,32 +250,24 @@ template <typename TC, typename TO, int ST, typename RD>
 __device__ __forceinline__ void gen_store(const LineArgs<TC>& A, const GenTile& G, int tid,
                                           int nthr, const RD& rd) {
   TO* __restrict__ out = reinterpret_cast<TO*>(A.out);
-  batched<4, double>(
-      G.C * G.N, tid, nthr,
-      [&](int e) -> double {
-        if (ST != ST_ACCUM) return 0.0;
-        int c, n;
-        G.split(e, &c, &n);
-        return c < G.nval ? A.rphi[G.at(e, c, n)] : 0.0;
-      },
-      [&](int e, double old) {
-        int c, n;
-        G.split(e, &c, &n);
-        if (c >= G.nval) return;
-        const TC v = rd(c, n);
-        if (ST == ST_ACCUM)
-          reinterpret_cast<double*>(A.out)[G.at(e, c, n)] = old + (double)v;
-        else
-          out[G.at(e, c, n)] = (TO)v;
-      });
+  for (int e = tid; e < G.C * G.N; e += nthr) {
+    int c, n;
+    G.split(e, &c, &n);
+    if (c >= G.nval) continue;
+    const int64_t p = G.at(e, c, n);
+    const TC v = rd(c, n);
+    if (ST == ST_ACCUM)
+      reinterpret_cast<double*>(A.out)[p] = A.rphi[p] + (double)v;
+    else
+      out[p] = (TO)v;
+  }
 }
 
 // Copies the half-length twiddles into LDS (A.ltw).
 template <typename TC>
 __device__ __forceinline__ void stage_twiddles(cplx<TC>* twl, const cplx<TC>* __restrict__ twH,
                                                int H, int tid, int nthr) {
-  batched<2, cplx<TC>>(H, tid, nthr, [&](int e) { return twH[e]; },
-                       [&](int e, cplx<TC> w) { twl[e] = w; });
+  for (int e = tid; e < H; e += nthr) twl[e] = twH[e];
 }
 
 // Forward post-processing of pair k (0 <= k <= H/2) of one line: from the
@@ -329,7 +314,7 @@ __device__ __forceinline__ void pre_pair(TC xk, TC xnk, TC xhk, TC xhpk, int k, 
 // LDS, the mixed-radix FFT above, pairs (k, H-k) of the real-FFT split per
 // thread.  Two LDS buffers of C lines each.  With H odd no pair is its own
 // partner; with H even the pair k = H/2 is.
-template <typename TC, typename TI, typename TO, int OP, int LD, int ST, int B>
+template <typename TC, typename TI, typename TO, int OP, int LD, int ST, int B, bool SUM>
 __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (A.skip && *A.skip) return;
@@ -346,15 +331,13 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
 
   // ---- load ----------------------------------------------------------------
   const double sub = A.sub ? *A.sub : 0.0;
-  if (A.ltw) stage_twiddles(twl, A.tab.twH, H, tid, nthr);
-  batched<LD == LD_RESID ? 2 : 4, TC>(
-      C * N, tid, nthr,
-      [&](int e) { return gen_load<TC, TI, LD, false>(A, G, in, sub, e); },
-      [&](int e, TC v) {
-        int c, n;
-        G.split(e, &c, &n);
-        s[c * ls + (OP == OP_INV ? n : mk_pos(n, N))] = v;
-      });
+  if (SUM && A.ltw) stage_twiddles(twl, A.tab.twH, H, tid, nthr);
+  for (int e = tid; e < C * N; e += nthr) {
+    int c, n;
+    G.split(e, &c, &n);
+    const TC v = gen_load<TC, TI, LD, false>(A, G, in, sub, e, c, n);
+    s[c * ls + (OP == OP_INV ? n : mk_pos(n, N))] = v;
+  }
   __syncthreads();
 
   cplx<TC>* zc = reinterpret_cast<cplx<TC>*>(s);
@@ -392,9 +375,9 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
       }
     }
     __syncthreads();
-    res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
+    res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
   } else {
-    const cplx<TC>* zf = fft_lds_mixed<TC, false>(zc, zc2, lsc, C, H, A, twl, tid, nthr);
+    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr);
     constexpr int PB = 2 * B + 1;
     TC xa[PB], xb[PB], xc[PB], xd[PB];
     int ck[PB], kk[PB];
@@ -445,7 +428,7 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
         }
       }
       __syncthreads();
-      res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
+      res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
     } else {
       __syncthreads();
 #pragma unroll
@@ -481,7 +464,7 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
 // spectrum with the same split, runs the inverse FFT and scales by 1/H.
 // C lines per workgroup in two LDS buffers; lines past the end of a partial
 // tile are masked.
-template <typename TC, typename TI, typename TO, int OP, int LD, int ST>
+template <typename TC, typename TI, typename TO, int OP, int LD, int ST, bool SUM>
 __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (A.skip && *A.skip) return;
@@ -501,20 +484,18 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   const AxisTables<TC>& Tb = A.tab;
   const GenTile G = gen_tile(A, t);
   const double sub = A.sub ? *A.sub : 0.0;
-  if (A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
+  if (SUM && A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
 
   if (OP != OP_INV) {
-    batched<LD == LD_RESID ? 2 : 4, TC>(
-        C * n, tid, nthr,
-        [&](int e) { return gen_load<TC, TI, LD, true>(A, G, in, sub, e); },
-        [&](int e, TC v) {
-          int c, i;
-          G.split(e, &c, &i);
-          s0[c * ls + i] = v;
-          if (i > 0 && i < n - 1) s0[c * ls + NS - i] = v;
-        });
+    for (int e = tid; e < C * n; e += nthr) {
+      int c, i;
+      G.split(e, &c, &i);
+      const TC v = gen_load<TC, TI, LD, true>(A, G, in, sub, e, c, i);
+      s0[c * ls + i] = v;
+      if (i > 0 && i < n - 1) s0[c * ls + NS - i] = v;
+    }
     __syncthreads();
-    const cplx<TC>* zf = fft_lds_mixed<TC, false>(reinterpret_cast<cplx<TC>*>(s0),
+    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(reinterpret_cast<cplx<TC>*>(s0),
                                                   reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
                                                   tid, nthr);
     if (reinterpret_cast<const TC*>(zf) != s0) {
@@ -561,14 +542,11 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
     }
     __syncthreads();
   } else {
-    batched<4, TC>(
-        C * n, tid, nthr,
-        [&](int e) { return gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e); },
-        [&](int e, TC v) {
-          int c, i;
-          G.split(e, &c, &i);
-          xs[c * ls + i] = v;
-        });
+    for (int e = tid; e < C * n; e += nthr) {
+      int c, i;
+      G.split(e, &c, &i);
+      xs[c * ls + i] = gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e, c, i);
+    }
     __syncthreads();
   }
   // inverse: Z[k] from the real spectrum (imaginary parts zero)
@@ -580,7 +558,7 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
   }
   __syncthreads();
   const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+      fft_lds_mixed<TC, true, SUM>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
   gen_store<TC, TO, ST>(A, G, tid, nthr,
                         [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
@@ -592,7 +570,7 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
 // split X_k = E_k + w^k O_k, w = exp(-2 pi i / N); the inverse runs the same
 // steps backwards and scales by 1/H.  C lines per workgroup in two LDS
 // buffers; lines past the end of a partial tile are masked.
-template <typename TC, typename TI, typename TO, int OP, int LD, int ST>
+template <typename TC, typename TI, typename TO, int OP, int LD, int ST, bool SUM>
 __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (A.skip && *A.skip) return;
@@ -613,19 +591,16 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   const AxisTables<TC>& Tb = A.tab;
   const GenTile G = gen_tile(A, t);
   const double sub = A.sub ? *A.sub : 0.0;
-  if (A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
+  if (SUM && A.ltw) stage_twiddles(twl, Tb.twH, H, tid, nthr);
 
   if (OP != OP_INV) {
-    batched<LD == LD_RESID ? 2 : 4, TC>(
-        C * N, tid, nthr,
-        [&](int e) { return gen_load<TC, TI, LD, false>(A, G, in, sub, e); },
-        [&](int e, TC v) {
-          int c, i;
-          G.split(e, &c, &i);
-          s0[c * ls + i] = v;
-        });
+    for (int e = tid; e < C * N; e += nthr) {
+      int c, i;
+      G.split(e, &c, &i);
+      s0[c * ls + i] = gen_load<TC, TI, LD, false>(A, G, in, sub, e, c, i);
+    }
     __syncthreads();
-    const cplx<TC>* zf = fft_lds_mixed<TC, false>(reinterpret_cast<cplx<TC>*>(s0),
+    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(reinterpret_cast<cplx<TC>*>(s0),
                                                   reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
                                                   tid, nthr);
     if (reinterpret_cast<const TC*>(zf) != s0) {
@@ -669,14 +644,11 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
     }
     __syncthreads();
   } else {
-    batched<4, TC>(
-        C * N, tid, nthr,
-        [&](int e) { return gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e); },
-        [&](int e, TC v) {
-          int c, i;
-          G.split(e, &c, &i);
-          xs[c * ls + i] = v;
-        });
+    for (int e = tid; e < C * N; e += nthr) {
+      int c, i;
+      G.split(e, &c, &i);
+      xs[c * ls + i] = gen_load<TC, TI, LD_PLAIN, false>(A, G, in, sub, e, c, i);
+    }
     __syncthreads();
   }
   cplx<TC>* za = reinterpret_cast<cplx<TC>*>(zs);
@@ -689,7 +661,7 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
   }
   __syncthreads();
   const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+      fft_lds_mixed<TC, true, SUM>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
   gen_store<TC, TO, ST>(A, G, tid, nthr,
                         [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
@@ -879,6 +851,13 @@ int generic_radices(int H, int* rad) {
   return H == 1 ? n : -1;
 }
 
+// Whether the FFT of half length H needs direct sums (the kernels' SUM).
+bool direct_sums(int H, size_t elem, const int* rad, int nrad) {
+  for (int i = 0; i < nrad; ++i)
+    if (rad[i] >= 11 || (rad[i] == 7 && sums7(H, elem))) return true;
+  return false;
+}
+
 // Whether a pass keeps its half-length twiddles in LDS as well: for the direct
 // sums of a prime factor of 11 or more, which read one per term (402^2 sub-step
 // 557 us against 637, 190 x 184 x 176 float32 solve 295 against 353); not on
@@ -1018,6 +997,17 @@ PassTiles pass_tiles(const pc_plan* P, int axis, size_t elem) {
 
 namespace {
 
+template <typename TC>
+int launch_lines(void (*fn)(LineArgs<TC>), const LineArgs<TC>& A, unsigned ntile, int nthr,
+                 size_t lds, hipStream_t s) {
+  if (lds > 65536)
+    PC_HIP_CHECK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds));
+  hipLaunchKernelGGL(fn, dim3(ntile), dim3(nthr), lds, s, A);
+  PC_HIP_CHECK(hipGetLastError());
+  return PC_OK;
+}
+
 template <typename TC, typename TI, typename TO, int OP, int LD, int ST>
 int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTables<TC>* tabs,
                 const double* rb, const double* rphi, double* bmean, hipStream_t s,
@@ -1101,13 +1091,11 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     int nthr = std::min(1024, std::max(128, C * Hv / 2));
     nthr = (nthr + 63) / 64 * 64;
     const size_t lds = (size_t)C * per_line + tw;
-    const void* fn = (const void*)dct1_lines<TC, TI, TO, OP, LD, ST>;
-    if (lds > 65536)
-      PC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((dct1_lines<TC, TI, TO, OP, LD, ST>), dim3((unsigned)ntile), dim3(nthr), lds,
-                       s, A);
-    PC_HIP_CHECK(hipGetLastError());
-    return PC_OK;
+    using Fn = void (*)(LineArgs<TC>);
+    const Fn fn = direct_sums(Hv, sizeof(TC), A.rad, A.nrad)
+                      ? (Fn)dct1_lines<TC, TI, TO, OP, LD, ST, true>
+                      : (Fn)dct1_lines<TC, TI, TO, OP, LD, ST, false>;
+    return launch_lines(fn, A, (unsigned)ntile, nthr, lds, s);
   }
   if (const int RT = rad_values(P, axis, sizeof(TC))) {
     // register kernel: T = H/RT threads per line, C lines per group
@@ -1166,13 +1154,11 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
     int nthr = std::min(1024, std::max(128, C * H / 2));
     nthr = (nthr + 63) / 64 * 64;
     const size_t lds = (size_t)C * per_line + tw;
-    const void* fn = (const void*)rdft_lines<TC, TI, TO, OP, LD, ST>;
-    if (lds > 65536)
-      PC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((rdft_lines<TC, TI, TO, OP, LD, ST>), dim3((unsigned)ntile), dim3(nthr), lds,
-                       s, A);
-    PC_HIP_CHECK(hipGetLastError());
-    return PC_OK;
+    using Fn = void (*)(LineArgs<TC>);
+    const Fn fn = direct_sums(H, sizeof(TC), A.rad, A.nrad)
+                      ? (Fn)rdft_lines<TC, TI, TO, OP, LD, ST, true>
+                      : (Fn)rdft_lines<TC, TI, TO, OP, LD, ST, false>;
+    return launch_lines(fn, A, (unsigned)ntile, nthr, lds, s);
   }
   A.nrad = generic_radices(H, A.rad);
   if (A.nrad < 0) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform length has too many factors");
@@ -1200,29 +1186,22 @@ int launch_pass(const pc_plan* P, int axis, const TI* in, TO* out, const AxisTab
   A.pad = ((size_t)C * (A.N + 2) * sizeof(TC) * 2 + tw <= (size_t)lds_limit()) ? 2 : 0;
   size_t lds = (size_t)C * (A.N + A.pad) * sizeof(TC) * 2 + tw;
   if (lds > (size_t)lds_limit()) return fail(PC_ERR_UNSUPPORTED_SIZE, "transform line too long");
-  dim3 grid(ntile), block(nthr);
-  const void* fn;
+  using Fn = void (*)(LineArgs<TC>);
+  Fn fn;
+  const bool sum = direct_sums(H, sizeof(TC), A.rad, A.nrad);
+#define PC_DCT_CASE(B)                                        \
+  case B:                                                     \
+    fn = sum ? (Fn)dct_lines<TC, TI, TO, OP, LD, ST, B, true> \
+             : (Fn)dct_lines<TC, TI, TO, OP, LD, ST, B, false>; \
+    break
   switch (B) {
-    case 1: fn = (const void*)dct_lines<TC, TI, TO, OP, LD, ST, 1>; break;
-    case 2: fn = (const void*)dct_lines<TC, TI, TO, OP, LD, ST, 2>; break;
-    case 4: fn = (const void*)dct_lines<TC, TI, TO, OP, LD, ST, 4>; break;
+    PC_DCT_CASE(1);
+    PC_DCT_CASE(2);
+    PC_DCT_CASE(4);
     default: return fail(PC_ERR_UNSUPPORTED_SIZE, "transform tile shape");
   }
-  if (lds > 65536)
-    PC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  switch (B) {
-    case 1:
-      hipLaunchKernelGGL((dct_lines<TC, TI, TO, OP, LD, ST, 1>), grid, block, lds, s, A);
-      break;
-    case 2:
-      hipLaunchKernelGGL((dct_lines<TC, TI, TO, OP, LD, ST, 2>), grid, block, lds, s, A);
-      break;
-    default:
-      hipLaunchKernelGGL((dct_lines<TC, TI, TO, OP, LD, ST, 4>), grid, block, lds, s, A);
-      break;
-  }
-  PC_HIP_CHECK(hipGetLastError());
-  return PC_OK;
+#undef PC_DCT_CASE
+  return launch_lines(fn, A, (unsigned)ntile, nthr, lds, s);
 }
 
 // Full solve with compute type TC from TI input to TO output.  Forward
