@@ -880,6 +880,40 @@ static bool float_noise(const pc_plan* P, size_t elem) {
   return elem == 4 && P->d == 2 && std::max(P->n[0], P->n[1]) > 512;
 }
 
+namespace {
+// Largest power of two not above v (v >= 1).
+int floor_pow2(int v) {
+  int c = 1;
+  while (2 * c <= v) c <<= 1;
+  return c;
+}
+
+// Lengths with a radix-10 plan.
+bool rad10_length(int N) { return N == 200 || N == 400 || N == 1000 || N == 2000; }
+
+// Lines per workgroup tile of the register transform with RT values per thread.
+int rad_lines(const pc_plan* P, int axis, size_t elem, int RT) {
+  const int N = P->n[axis];
+  const int H = N / 2, T = H / RT, LS = H + H / 16 + 1;
+  const int64_t lines = P->G / N;
+  int C;
+  // C (a power of two) divides the row count (rows) or the x extent
+  // (strided lines), which need not be powers of two when another axis is
+  // not
+  if (axis == 0) {
+    C = floor_pow2(std::max(1, ROW_THREADS / T));
+    while (C > 1 && ((int64_t)C > lines || lines % C)) C >>= 1;
+  } else {
+    C = (int)(128 / elem);
+    while (C > 1 && (C * T > COL_MAX_THREADS || C > P->n[0] || P->n[0] % C)) C >>= 1;
+  }
+  while (C > 1 && (size_t)C * LS * 2 * elem > (size_t)lds_limit()) C >>= 1;
+  // small grids (the 400 x 400 grid of Sec. 3): fewer lines per group, so
+  // that every compute unit gets work
+  return fill_device(C, lines / C);
+}
+}  // namespace
+
 // Radix 4 where a pass is bound by a wavefront's own instructions and latency
 // rather than by the device: on every axis of grids of up to 2^20 points, which
 // leave the radix-8 plan at most one wavefront per SIMD (N up to 1024 on the
@@ -904,48 +938,34 @@ int rad_values(const pc_plan* P, int axis, size_t elem) {
                    : (axis < P->d - 1 ? (small ? 512 : 256) : (small ? 1024 : 0));
   if (N >= 32 && N <= lim4 && pow2(N) && !float_noise(P, elem)) return 4;
   if (N >= 32 && N <= 4096 && pow2(N)) return 8;
-  // The radix-10 plan's 20 threads a line of 400 points leave the fused last
-  // axis of a small grid at 17.4 us where the generic kernel, with a thread
-  // per two points, takes 13.6 (400^2 periodic sub-step 389 -> 356 us, 200^2
-  // 260 -> 247); a Neumann axis of 400 is equal (13.0 us), longer ones slower.
-  if (small && axis == P->d - 1 && (N == 200 || (N == 400 && P->bc[axis] == PC_BC_PERIODIC)))
-    return 0;
-  if (N == 200 || N == 400 || N == 1000 || N == 2000) return 10;
-  return 0;
+  if (!rad10_length(N)) return 0;
+  // The fused last axis of a small grid runs the generic kernel, with a thread
+  // per two points, where the radix-10 one takes longer (solves, radix 10 ->
+  // generic):
+  //  - periodic in float64, whose radix-10 kernel spills 430-480 bytes a thread:
+  //    400^2 29.6 -> 25.7 us, 200 x 1000 30.4 -> 27.3, 400 x 2000 48.9 -> 43.8,
+  //    64 x 64 x 200 53.6 -> 45.3 (on larger grids the spills are hidden:
+  //    64 x 64 x 400 76.9 -> 82.5); in float32 they are 20-44 bytes: 400^2
+  //    22.7 -> 24.1, 64 x 64 x 200 31.8 -> 34.7
+  //  - Neumann in 2D, where a radix-10 workgroup has less than half a wavefront
+  //    of threads (10 or 20): 200^2 25.5 -> 23.2, 400 x 200 30.4 -> 24.8,
+  //    1000 x 400 30.7 -> 28.9; with 40 or more 2000 x 400 37.8 -> 38.5,
+  //    200 x 1000 27.2 -> 31.3; in 3D with 20 32 x 32 x 200 30.0 -> 30.6.
+  if (small && axis == P->d - 1) {
+    if (P->bc[axis] == PC_BC_PERIODIC) {
+      if (elem == 8) return 0;
+    } else if (P->d == 2 && rad_lines(P, axis, elem, 10) * (N / 20) < 32) {
+      return 0;
+    }
+  }
+  return 10;
 }
-
-namespace {
-// Largest power of two not above v (v >= 1).
-int floor_pow2(int v) {
-  int c = 1;
-  while (2 * c <= v) c <<= 1;
-  return c;
-}
-}  // namespace
 
 // Lines per workgroup tile of the register transform along `axis` (0 when
-// the axis uses the generic kernel: N < 32 or not a power of two).
+// the axis uses the generic kernel, rad_values).
 int rad_tile_lines(const pc_plan* P, int axis, size_t elem) {
-  const int N = P->n[axis];
   const int RT = rad_values(P, axis, elem);
-  if (!RT) return 0;
-  const int H = N / 2, T = H / RT, LS = H + H / 16 + 1;
-  const int64_t lines = P->G / N;
-  int C;
-  // C (a power of two) divides the row count (rows) or the x extent
-  // (strided lines), which need not be powers of two when another axis is
-  // not
-  if (axis == 0) {
-    C = floor_pow2(std::max(1, ROW_THREADS / T));
-    while (C > 1 && ((int64_t)C > lines || lines % C)) C >>= 1;
-  } else {
-    C = (int)(128 / elem);
-    while (C > 1 && (C * T > COL_MAX_THREADS || C > P->n[0] || P->n[0] % C)) C >>= 1;
-  }
-  while (C > 1 && (size_t)C * LS * 2 * elem > (size_t)lds_limit()) C >>= 1;
-  // small grids (the 400 x 400 grid of Sec. 3): fewer lines per group, so
-  // that every compute unit gets work
-  return fill_device(C, lines / C);
+  return RT ? rad_lines(P, axis, elem, RT) : 0;
 }
 
 // Lines per workgroup tile of the generic kernel for a Neumann axis (the
