@@ -153,12 +153,14 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
   // the point's own streams first: they are in flight while the nodes are
   // gathered
   const GridRows<D> R = load_rows<D>(A, P);
-  constexpr int KW = K > 0 ? (K + 1) / 2 : 1;
-  uint32_t w[KW];
-  if (K > 0) {
+  // other sizes than the defaults: in 3D the largest stencil's places and
+  // entries, guarded (160^3, k = 20: 344 -> 290 us, k = 32 468 -> 384); in 2D,
+  // where the registers cost waves (1024^2, k = 9: 33 -> 34 us), a loop
+  constexpr int KU = K > 0 ? K : (D == 3 ? PC_MAX_K_GRID : 0);
+  uint32_t w[KU > 0 ? (KU + 1) / 2 : 1];
 #pragma unroll
-    for (int i = 0; i < KW; ++i) w[i] = (uint32_t)ldnt(blk + i * TP + P.t);
-  }
+  for (int i = 0; i < (KU + 1) / 2; ++i)
+    if (2 * i < k) w[i] = (uint32_t)ldnt(blk + i * TP + P.t);
   // positions and values of the tile's nodes into LDS
   for (int s = threadIdx.x; s < n; s += TP) {
     const int64_t j = blk[tile_words(D, k) + s];
@@ -199,9 +201,10 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
       }
       entry(f, std::false_type{});
     };
-    if constexpr (K > 0) {
+    if constexpr (KU > 0) {
 #pragma unroll
-      for (int i = 0; i < K; ++i) place((i & 1) ? w[i / 2] >> 16 : w[i / 2] & 0xffffu);
+      for (int i = 0; i < KU; ++i)
+        if (i < k) place((i & 1) ? w[i / 2] >> 16 : w[i / 2] & 0xffffu);
     } else {
       for (int i = 0; i < k; ++i) {
         const uint32_t wi = (uint32_t)ldnt(blk + (i / 2) * TP + P.t);
