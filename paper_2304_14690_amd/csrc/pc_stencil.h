@@ -315,7 +315,7 @@ constexpr int tile_cap(int d, int k) {
 struct GridFit {
   int32_t n[3], nt[3];     // grid points and tiles per axis
   int32_t k;
-  int32_t direct;          // no tile lists (eps beyond row_weight's range)
+  int32_t clamp;           // row_weight's exponent needs its clamp
   double off, h[3];
   double L[3], iL[3];      // box length and its inverse on periodic axes, else 0
   int64_t ms;
@@ -463,7 +463,8 @@ __device__ __forceinline__ void grid_offset(const GridFit& A, const double (&x)[
 // exp(-alpha |t|^2) as 2^y, y = -alpha log2(e) |t|^2 = k + f, |f| <= 1/2: the
 // product is never rounded on its own (both uses are fused), and the degree-11
 // polynomial (the minimax fit of (2^f - 1 - f ln 2) / f^2) leaves 1e-17.
-// Without CLAMP y must stay above -1022 (alpha |t|^2 <= eps: GridFit.direct).
+// Without CLAMP y must stay above -1022; alpha |t|^2 <= eps, so it does up to
+// eps = 690 (GridFit.clamp; two more operations an entry than without).
 template <int D, bool CLAMP>
 __device__ __forceinline__ double row_weight(const GridRows<D>& R, const double (&t)[D]) {
   constexpr double MAGIC = 6755399441055744.0;  // 1.5 2^52
@@ -471,8 +472,10 @@ __device__ __forceinline__ double row_weight(const GridRows<D>& R, const double 
   double r2 = t[0] * t[0];
 #pragma unroll
   for (int a = 1; a < D; ++a) r2 = __builtin_fma(t[a], t[a], r2);
-  const double m = __builtin_fma(na, r2, MAGIC);
-  const double f = __builtin_fma(na, r2, MAGIC - m);
+  double m = __builtin_fma(na, r2, MAGIC);
+  if (CLAMP) m = fmax(m, MAGIC - 1000.0);
+  double f = __builtin_fma(na, r2, MAGIC - m);
+  if (CLAMP) f = fmax(f, -0.5);
   double p = 4.4541068401718916193e-10;
   p = __builtin_fma(p, f, 7.0709843005464476907e-9);
   p = __builtin_fma(p, f, 1.0178067252442298443e-7);
@@ -486,8 +489,7 @@ __device__ __forceinline__ double row_weight(const GridRows<D>& R, const double 
   p = __builtin_fma(p, f, 6.9314718055994530942e-1);
   p = __builtin_fma(p, f, 1.0);
   // the low word of m is k
-  int k = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
-  if (CLAMP) k = max(k, -1000);
+  const int k = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
   const uint64_t pb = __builtin_bit_cast(uint64_t, p);
   const uint32_t hi = (uint32_t)(pb >> 32) + ((uint32_t)k << 20);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)pb);

@@ -51,7 +51,7 @@ GridFit grid_fit_args(const pc_geom* g) {
   const int d = g->d;
   A.off = g->vertex ? 0.0 : 0.5;
   A.k = g->k_grid;
-  A.direct = g->eps > 690.0;
+  A.clamp = g->eps > 690.0;
   A.ms = g->ms;
   A.blk = g->gblk;
   A.cnt = g->gcnt;
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_stored(GridFit A,
 // four) take 2.78 and 2.73 ms against 2.63, 8 x 4 x 4 2.87; sweeping the tiles
 // in slabs along y, so that an XCD's L2 holds the planes tiles share, changes
 // nothing (2.72-2.78).
-template <typename T, int D, int K, bool PER>
+template <typename T, int D, int K, bool PER, bool CLAMP>
 __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* __restrict__ v,
                                                             int64_t M, T* __restrict__ b, int cap) {
   constexpr int TP = tile_points(D);
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
   // gathered
   const GridRows<D> R = load_rows<D>(A, P);
   // other sizes than the defaults: in 3D the largest stencil's places and
-  // entries, guarded (160^3, k = 20: 344 -> 290 us, k = 32 468 -> 384); in 2D,
+  // entries, guarded (160^3, k = 20: 344 -> 286 us, k = 32 468 -> 375); in 2D,
   // where the registers cost waves (1024^2, k = 9: 33 -> 34 us), a loop
   constexpr int KU = K > 0 ? K : (D == 3 ? PC_MAX_K_GRID : 0);
   uint32_t w[KU > 0 ? (KU + 1) / 2 : 1];
@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
         f[2 * a] = q.x;
         f[2 * a + 1] = q.y;
       }
-      entry(f, std::false_type{});
+      entry(f, std::bool_constant<CLAMP>{});
     };
     if constexpr (KU > 0) {
 #pragma unroll
@@ -919,11 +919,14 @@ int launch_div_all(const pc_geom* g, const T* v, T* b, hipStream_t s) {
   const size_t lds = (size_t)g->gmax * g->d * 16;
 #define DIVL(D, K)                                                                             \
   do {                                                                                         \
-    if (g->per)                                                                                \
-      hipLaunchKernelGGL((k_div_all<T, D, K, true>), grid, block, lds, s, gf, v, g->M, b,       \
+    if (gf.clamp)                                                                              \
+      hipLaunchKernelGGL((k_div_all<T, D, K, true, true>), grid, block, lds, s, gf, v, g->M, b, \
+                         g->gmax);                                                             \
+    else if (g->per)                                                                           \
+      hipLaunchKernelGGL((k_div_all<T, D, K, true, false>), grid, block, lds, s, gf, v, g->M, b, \
                          g->gmax);                                                             \
     else                                                                                       \
-      hipLaunchKernelGGL((k_div_all<T, D, K, false>), grid, block, lds, s, gf, v, g->M, b,      \
+      hipLaunchKernelGGL((k_div_all<T, D, K, false, false>), grid, block, lds, s, gf, v, g->M, b, \
                          g->gmax);                                                             \
   } while (0)
   if (g->d == 2) {

@@ -1028,7 +1028,7 @@ __global__ void __launch_bounds__(tile_points(D)) k_tile_pack(GridFit A, int32_t
   constexpr int TP = tile_points(D);
   __shared__ int32_t hash[TILE_HASH], list[TILE_SORT];
   __shared__ int32_t nu, nl;
-  const int k = A.k, cap = A.direct ? 0 : tile_cap(D, k);
+  const int k = A.k, cap = tile_cap(D, k);
   const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
   int32_t* const b = blk + P.tile * ((int64_t)k * TP);
   const bool in = P.inside(A);
