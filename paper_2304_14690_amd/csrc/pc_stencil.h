@@ -284,8 +284,8 @@ __device__ __forceinline__ void block_coef(const NodeFit& A, const BlockFit<D, M
 // 28 (3D) float64 per grid point instead of 32 or 81 per precision.
 constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
 
-// The grid points are stored by tiles of tile_x * tile_y * tile_z points (one
-// workgroup each).  The stencils of a tile share most of their nodes (1.7
+// The grid points are stored by tiles of 256 points (one workgroup each), their
+// shape by the grid (tile_shape).  The stencils of a tile share most of their nodes (1.7
 // distinct ones per point in 2D and 2.9 in 3D against 16 and 27 entries), so
 // a tile keeps the ascending list of its nodes and each stencil entry is a
 // 16-bit place in that list: a workgroup gathers every node once into LDS and
@@ -294,10 +294,34 @@ constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
 // word, [ceil(k/2)][TP], then the list; where a tile has
 // more nodes than tile_cap (a cloud much finer than the grid) its count is -1
 // and the block holds the node indices themselves, [k][TP].
-constexpr int tile_x(int d) { return d == 2 ? 32 : 16; }
-constexpr int tile_y(int d) { return d == 2 ? 8 : 4; }
-constexpr int tile_z(int d) { return d == 2 ? 1 : 4; }
-constexpr int tile_points(int d) { return tile_x(d) * tile_y(d) * tile_z(d); }
+constexpr int TILE_LOG = 8;
+constexpr int tile_points(int) { return 1 << TILE_LOG; }
+
+// Points of a tile per axis, as powers of two: 32 x 8 and 16 x 4 x 4, or a shape
+// that covers a thin or short grid with fewer tiles: the padding points of a
+// tile hold rows and places and take threads like the others.  Another shape
+// has to save more than an eighth of the tiles, since its nodes are more (32 x
+// 2 x 4) or no fewer (8 x 8 x 4).
+struct TileShape {
+  int lx, ly, lz;
+
+  int64_t tiles(const int32_t* n) const {
+    return ((int64_t)n[0] + (1 << lx) - 1 >> lx) * ((int64_t)n[1] + (1 << ly) - 1 >> ly) *
+           (lx + ly == TILE_LOG ? 1 : (int64_t)n[2] + (1 << lz) - 1 >> lz);
+  }
+};
+
+inline TileShape tile_shape(int d, const int32_t* n) {
+  constexpr TileShape S2[] = {{5, 3, 0}, {4, 4, 0}, {3, 5, 0}, {6, 2, 0}};
+  constexpr TileShape S3[] = {{4, 2, 2}, {3, 3, 2}, {3, 2, 3}, {4, 1, 3}, {4, 3, 1},
+                              {5, 1, 2}, {5, 2, 1}};
+  TileShape best = d == 2 ? S2[0] : S3[0];
+  for (const TileShape& t : S2)
+    if (d == 2 && 8 * t.tiles(n) < 7 * best.tiles(n)) best = t;
+  for (const TileShape& t : S3)
+    if (d == 3 && 8 * t.tiles(n) < 7 * best.tiles(n)) best = t;
+  return best;
+}
 // Words of places in a tile's block.
 constexpr int64_t tile_words(int d, int k) { return (int64_t)(k + 1) / 2 * tile_points(d); }
 // LDS bytes from one node to the next: pairs (x, y), (v_x, v_y) in two planes
@@ -314,6 +338,7 @@ constexpr int tile_cap(int d, int k) {
 
 struct GridFit {
   int32_t n[3], nt[3];     // grid points and tiles per axis
+  int32_t lx, ly;          // points of a tile per axis (TileShape)
   int32_t k;
   int32_t clamp;           // row_weight's exponent needs its clamp
   double off, h[3];
@@ -336,10 +361,7 @@ struct GridFit {
 inline bool grid_rows_kept(int d, int64_t G, int64_t M) { return M <= (d == 2 ? 5 : 2) * G; }
 
 GridFit grid_fit_args(const pc_geom* g);
-inline int64_t grid_tiles(int d, const int32_t* n) {
-  return (int64_t)((n[0] + tile_x(d) - 1) / tile_x(d)) * ((n[1] + tile_y(d) - 1) / tile_y(d)) *
-         (d == 3 ? (n[2] + tile_z(d) - 1) / tile_z(d) : 1);
-}
+inline int64_t grid_tiles(int d, const int32_t* n) { return tile_shape(d, n).tiles(n); }
 
 // A grid point by tile and place in the tile.
 template <int D>
@@ -369,10 +391,10 @@ __device__ __forceinline__ TilePoint<D> tile_point(const GridFit& A, int64_t til
   const int tx = (int)((uint32_t)tile - r * (uint32_t)A.nt[0]);
   const int tz = D == 3 ? (int)(r / (uint32_t)A.nt[1]) : 0;
   const int ty = (int)r - tz * A.nt[1];
-  constexpr int X = tile_x(D), Y = tile_y(D);
-  P.c[0] = tx * X + t % X;
-  P.c[1] = ty * Y + (t / X) % Y;
-  P.c[2] = D == 3 ? tz * tile_z(D) + t / (X * Y) : 0;
+  const int ly = D == 2 ? TILE_LOG - A.lx : A.ly;
+  P.c[0] = (tx << A.lx) + (t & ((1 << A.lx) - 1));
+  P.c[1] = (ty << ly) + ((t >> A.lx) & ((1 << ly) - 1));
+  P.c[2] = D == 3 ? (tz << (TILE_LOG - A.lx - ly)) + (t >> (A.lx + ly)) : 0;
   return P;
 }
 
@@ -384,9 +406,10 @@ __device__ __forceinline__ TilePoint<D> tile_point_of(const GridFit& A, int64_t 
   P.c[0] = (int)(p - r * A.n[0]);
   P.c[2] = D == 3 ? (int)(r / A.n[1]) : 0;
   P.c[1] = (int)(r - (int64_t)P.c[2] * A.n[1]);
-  constexpr int X = tile_x(D), Y = tile_y(D), Z = tile_z(D);
-  P.tile = ((int64_t)(P.c[2] / Z) * A.nt[1] + P.c[1] / Y) * A.nt[0] + P.c[0] / X;
-  P.t = ((P.c[2] % Z) * Y + P.c[1] % Y) * X + P.c[0] % X;
+  const int lx = A.lx, ly = A.ly, lz = TILE_LOG - lx - ly;
+  P.tile = ((int64_t)(P.c[2] >> lz) * A.nt[1] + (P.c[1] >> ly)) * A.nt[0] + (P.c[0] >> lx);
+  P.t = ((P.c[2] & ((1 << lz) - 1)) << (lx + ly)) + ((P.c[1] & ((1 << ly) - 1)) << lx) +
+        (P.c[0] & ((1 << lx) - 1));
   return P;
 }
 

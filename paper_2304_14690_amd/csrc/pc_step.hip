@@ -59,10 +59,13 @@ GridFit grid_fit_args(const pc_geom* g) {
   A.c64 = g->gcoef;
   A.c32 = g->gcoef32;
   A.x = g->xyz;
-  const int T[3] = {tile_x(d), tile_y(d), tile_z(d)};
+  const TileShape ts = tile_shape(d, g->n);
+  const int lt[3] = {ts.lx, ts.ly, ts.lz};
+  A.lx = ts.lx;
+  A.ly = ts.ly;
   for (int a = 0; a < 3; ++a) {
     A.n[a] = a < d ? g->n[a] : 1;
-    A.nt[a] = (A.n[a] + T[a] - 1) / T[a];
+    A.nt[a] = (A.n[a] + (1 << lt[a]) - 1) >> lt[a];
     A.h[a] = g->h[a];
     if (a < d && ((g->per >> a) & 1)) {
       A.L[a] = (double)g->n[a] * g->h[a];

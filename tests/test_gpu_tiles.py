@@ -1,5 +1,6 @@
 """The divergence from rows and tile node lists where its dispatch changes: a
-shape parameter beyond the range of the unclamped weight."""
+shape parameter beyond the range of the unclamped weight, and the tile shapes
+of thin and short grids."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,29 @@ def test_large_shape_parameter(pc, n, bc, kg, eps, support):
     eps / support^2 = 0.7)."""
     x, kind = lattice(n, 0.125, 8)
     check_divergence(pc, n, 0.125, bc, x, kind, kg, eps=eps, support=support)
+
+
+@pytest.mark.parametrize("n,bc", [
+    ((8, 70), (N, PER)), ((16, 34), (N, N)), ((40, 34), (PER, N)), ((70, 12), (N, N)),
+    ((72, 64), (N, N)), ((8, 10, 12), (N, N, PER)), ((8, 12, 16), (N, N, N)),
+    ((16, 10, 8), (N, PER, N)), ((18, 8, 10), (N, N, N)), ((32, 10, 12), (PER, N, N)),
+    ((32, 12, 10), (N, N, N)), ((24, 16, 12), (N, N, N)),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v[0], int) else "")
+def test_tile_shapes(pc, n, bc):
+    """Grids that end inside a tile or take another tile shape than 32 x 8 and
+    16 x 4 x 4."""
+    x, kind = lattice(n, 0.125, 8)
+    check_divergence(pc, n, 0.125, bc, x, kind, 16 if len(n) == 2 else 27)
+
+
+@pytest.mark.parametrize("n,m", [((8, 64), (64, 8)), ((16, 128), (128, 16)),
+                                 ((8, 32, 32), (32, 32, 8))],
+                         ids=["8x64", "16x128", "8x32x32"])
+def test_thin_grids_hold_no_padding(pc, n, m):
+    """A thin grid's geometry is as large as that of the same grid laid flat:
+    no tile reaches beyond it."""
+    size = []
+    for g in (n, m):
+        plan = pc.Plan(len(n), g, (0.125,) * len(n))
+        size.append(pc.geom_footprint(plan, int(np.prod(n)), 0, 0, 16, 16 if len(n) == 2 else 27)[0])
+    assert size[0] == size[1]
