@@ -291,9 +291,10 @@ constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
 // 16-bit place in that list: a workgroup gathers every node once into LDS and
 // the entries are read from there (a place is the byte offset of its first
 // pair there).  A tile's block of 4 k TP bytes holds the places, two to a
-// word, [ceil(k/2)][TP], then the list; where a tile has
-// more nodes than tile_cap (a cloud much finer than the grid) its count is -1
-// and the block holds the node indices themselves, [k][TP].
+// word, [ceil(k/2)][TP], then the list.  A tile with more nodes than a list
+// may hold (a cloud refined there) keeps its coefficients, in float64: its
+// block holds the node indices, [k][TP], and its count is the complement of
+// its place in GridFit.over.
 constexpr int TILE_LOG = 8;
 constexpr int tile_points(int) { return 1 << TILE_LOG; }
 
@@ -336,6 +337,20 @@ constexpr int tile_cap(int d, int k) {
   return (int)(cap < room ? cap : room);
 }
 
+// Nodes a 3D list may hold while the four workgroups that the registers allow
+// still share a compute unit's LDS.  All workgroups of a launch take the LDS of
+// its longest list, so a few denser tiles would slow the whole grid: up to 1 in
+// LIST_SHARE of the tiles keep coefficients instead, where there are more than
+// LIST_TILES (two generations of workgroups): 256^3 with surface points a third
+// of a spacing apart 1543 -> 1373 us, 160^3 347 -> 325; on 48^3, one generation,
+// 14 us with long lists and 19 with coefficients.  In 2D longer lists cost less
+// than coefficients (1024^2 with a refined patch, float64: 42 against 53 us).
+constexpr int LIST_NODES = 853, LIST_SHARE = 16, LIST_TILES = 2048;
+inline int list_nodes(int d, int k, int64_t ntile) {
+  const int cap = tile_cap(d, k);
+  return d == 3 && ntile > LIST_TILES && cap > LIST_NODES ? LIST_NODES : cap;
+}
+
 struct GridFit {
   int32_t n[3], nt[3];     // grid points and tiles per axis
   int32_t lx, ly;          // points of a tile per axis (TileShape)
@@ -347,17 +362,15 @@ struct GridFit {
   const int32_t* blk;      // [ntile][k * TP] words
   const int32_t* cnt;      // [ntile] nodes of the tile's list, or -1
   const double* rows;      // [ntile][grid_rows(d)][TP], or null: stored coefficients
+  const double* over;      // [][d * k][TP]: coefficients of tiles without a list
   const double* c64;       // [ntile][d * k][TP] (component a, entry i at a * k + i)
   const float* c32;        // or null
   const double* x;         // [d][ms] node positions
 };
 
-// Whether a geometry keeps rows.  A cloud much finer than the grid shares few
-// nodes between grid points: its tiles outgrow their LDS lists from about 6 G
-// (2D) or 2.4 G (3D) nodes on, and gathering position and value of every
-// entry from memory costs more than streaming stored coefficients (96^3 grid,
-// 8 nodes a cell: 593 against 218 us in float64, 487 against 149 in float32),
-// so such clouds keep those.
+// Whether a geometry keeps rows at all.  A cloud much finer than the grid shares
+// few nodes between grid points: its tiles outgrow their LDS lists from about
+// 6 G (2D) or 2.4 G (3D) nodes on, and it streams stored coefficients.
 inline bool grid_rows_kept(int d, int64_t G, int64_t M) { return M <= (d == 2 ? 5 : 2) * G; }
 
 GridFit grid_fit_args(const pc_geom* g);

@@ -56,6 +56,7 @@ GridFit grid_fit_args(const pc_geom* g) {
   A.blk = g->gblk;
   A.cnt = g->gcnt;
   A.rows = g->grow;
+  A.over = g->gover;
   A.c64 = g->gcoef;
   A.c32 = g->gcoef32;
   A.x = g->xyz;
@@ -137,7 +138,9 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_stored(GridFit A,
 // (k = 16, 184 bytes a point, 5.6 TB/s) 288 -> 137 us; float32 (the same
 // float64 coefficients) 200 x 168 x 120 386 -> 361 us, 2048^2 164 -> 121 us.
 // Gathering each entry's six values from memory instead of LDS costs 41
-// cycles a load and wave, 5.7 ms at 512 x 256 x 256.  Tiles of 16 x 8 x 4 and
+// cycles a load and wave, 5.7 ms at 512 x 256 x 256, so tiles without a list
+// stream float64 coefficients (160^3 with 6% of the box refined twofold: 697 ->
+// 473 us, float32 563 -> 429; 64^3 40 -> 32).  Tiles of 16 x 8 x 4 and
 // 8 x 8 x 8 points (512 threads, two workgroups a compute unit instead of
 // four) take 2.78 and 2.73 ms against 2.63, 8 x 4 x 4 2.87; sweeping the tiles
 // in slabs along y, so that an XCD's L2 holds the planes tiles share, changes
@@ -180,29 +183,25 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
   }
   double xt[D], acc = 0.0;
   P.position(A, xt);
-  auto entry = [&](const double (&f)[2 * D], auto clamp) {
-    double x[D], t[D], c[D];
-#pragma unroll
-    for (int a = 0; a < D; ++a) x[a] = f[a];
-    grid_offset<D, PER>(A, x, xt, t);
-    row_poly<D>(R, t, c);
-    double s = c[0] * f[D];
-#pragma unroll
-    for (int a = 1; a < D; ++a) s = __builtin_fma(c[a], f[D + a], s);
-    acc = __builtin_fma(row_weight<D, decltype(clamp)::value>(R, t), s, acc);
-  };
   __syncthreads();
   if (!P.inside(A)) return;
   if (n >= 0) {
     auto place = [&](uint32_t l) {
-      double f[2 * D];
+      double f[2 * D], x[D], t[D], c[D];
 #pragma unroll
       for (int a = 0; a < D; ++a) {
         const double2 q = *reinterpret_cast<const double2*>(node + l + a * pair);
         f[2 * a] = q.x;
         f[2 * a + 1] = q.y;
       }
-      entry(f, std::bool_constant<CLAMP>{});
+#pragma unroll
+      for (int a = 0; a < D; ++a) x[a] = f[a];
+      grid_offset<D, PER>(A, x, xt, t);
+      row_poly<D>(R, t, c);
+      double s = c[0] * f[D];
+#pragma unroll
+      for (int a = 1; a < D; ++a) s = __builtin_fma(c[a], f[D + a], s);
+      acc = __builtin_fma(row_weight<D, CLAMP>(R, t), s, acc);
     };
     if constexpr (KU > 0) {
 #pragma unroll
@@ -215,15 +214,13 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
       }
     }
   } else {
+    const double* const c = A.over + (int64_t)~n * (D * k * TP) + P.t;
+#pragma unroll (D == 3 ? 4 : 2)
     for (int i = 0; i < k; ++i) {
       const int64_t j = ldnt(blk + i * TP + P.t);
-      double f[2 * D];
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        f[a] = A.x[a * A.ms + j];
-        f[D + a] = (double)v[a * M + j];
-      }
-      entry(f, std::true_type{});
+      for (int a = 0; a < D; ++a)
+        acc = __builtin_fma(ldnt(c + (a * k + i) * TP), (double)v[a * M + j], acc);
     }
   }
   b[P.flat(A)] = (T)acc;

@@ -1017,19 +1017,23 @@ __global__ void __launch_bounds__(64) k_self_stencils(SelfStencilArgs SA) {
 // that gathering them is close to contiguous) and the entries' places in it
 // (pc_stencil.h), in the same block of memory: every index is in registers
 // before the block is written.  The distinct nodes are collected in a hash
-// table, sorted (bitonic) and looked up by bisection, all in LDS; gmax takes
-// the longest list.
+// table, sorted (bitonic) and looked up by bisection, all in LDS.  A tile of more
+// than cap nodes keeps its indices and gets the count -1; stat[0] takes the
+// longest list, stat[1] counts the tiles without one.  again: such tiles of an
+// earlier pass, with a higher cap.
 constexpr int TILE_HASH = 4096, TILE_SORT = 2048;
 
 template <int D>
 __global__ void __launch_bounds__(tile_points(D)) k_tile_pack(GridFit A, int32_t* __restrict__ blk,
-                                                              int32_t* __restrict__ cnt,
-                                                              int32_t* __restrict__ gmax) {
+                                                              int32_t* __restrict__ cnt, int cap,
+                                                              bool again,
+                                                              int32_t* __restrict__ stat) {
   constexpr int TP = tile_points(D);
   __shared__ int32_t hash[TILE_HASH], list[TILE_SORT];
   __shared__ int32_t nu, nl;
-  const int k = A.k, cap = tile_cap(D, k);
+  const int k = A.k;
   const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
+  if (again && cnt[P.tile] >= 0) return;
   int32_t* const b = blk + P.tile * ((int64_t)k * TP);
   const bool in = P.inside(A);
   for (int i = threadIdx.x; i < TILE_HASH; i += TP) hash[i] = -1;
@@ -1054,7 +1058,10 @@ __global__ void __launch_bounds__(tile_points(D)) k_tile_pack(GridFit A, int32_t
   __syncthreads();
   const int n = nu;
   if (n > cap) {
-    if (threadIdx.x == 0) cnt[P.tile] = -1;
+    if (threadIdx.x == 0) {
+      cnt[P.tile] = -1;
+      atomicAdd(&stat[1], 1);
+    }
     return;
   }
   int n2 = 64;
@@ -1095,7 +1102,31 @@ __global__ void __launch_bounds__(tile_points(D)) k_tile_pack(GridFit A, int32_t
   for (int i = threadIdx.x; i < n; i += TP) out[i] = list[i];
   if (threadIdx.x == 0) {
     cnt[P.tile] = n;
-    atomicMax(gmax, n);
+    atomicMax(&stat[0], n);
+  }
+}
+
+// Numbers the tiles without a list (cnt becomes the complement of the number).
+__global__ void __launch_bounds__(256) k_tile_number(int32_t* __restrict__ cnt, int64_t ntile,
+                                                     int32_t* __restrict__ next) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t < ntile && cnt[t] < 0) cnt[t] = ~atomicAdd(next, 1);
+}
+
+// Their coefficients.
+template <int D>
+__global__ void __launch_bounds__(tile_points(D)) k_tile_coefs(GridFit A, double* __restrict__ over) {
+  constexpr int TP = tile_points(D);
+  const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
+  const int32_t n = A.cnt[P.tile];
+  if (n >= 0 || !P.inside(A)) return;
+  double xt[D], c[D];
+  P.position(A, xt);
+  double* const out = over + (int64_t)~n * (D * A.k * TP) + P.t;
+  for (int i = 0; i < A.k; ++i) {
+    grid_coef<D>(A, P, xt, i, grid_node<D>(A, P, i), c);
+#pragma unroll
+    for (int a = 0; a < D; ++a) out[(a * A.k + i) * TP] = c[a];
   }
 }
 
@@ -1288,8 +1319,8 @@ unsigned nblocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void geom_free(pc_geom* g) {
   if (!g) return;
-  void* ptrs[] = {g->gblk,   g->gcnt,   g->grow,   g->gcoef,  g->gcoef32, g->nbase,   g->ncoef,  g->ncoef32,
-                  g->ib,     g->near,   g->nslot,   g->ncoefib, g->ncoefib32, g->ibbase,
+  void* ptrs[] = {g->gblk,   g->gcnt,   g->grow,    g->gover,  g->gcoef,    g->gcoef32,
+                  g->nbase,  g->ncoef,  g->ncoef32, g->ib,     g->near,   g->nslot,   g->ncoefib, g->ncoefib32, g->ibbase,
                   g->ibcoef, g->ibcoef32, g->sidx,  g->scoef,   g->scoef32,  g->vlist,
                   g->perm,   g->xyz,    g->ibx};
   for (void* p : ptrs) dev_free(p);
@@ -1602,17 +1633,24 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
 
   // tile lists (every grid point has its k_grid nodes: the flags are clear)
   const GridFit gf = grid_fit_args(g);
-  int32_t* gmax = bad + 1;
-  if (!g->gfit)
-    PC_HIP_CHECK(hipMemsetAsync(g->gcnt, 0xff, (size_t)ntile * 4, s));
-  else if (d == 2)
-    hipLaunchKernelGGL(k_tile_pack<2>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk, g->gcnt,
-                       gmax);
+  int32_t* const stat = bad + 1;  // longest list, tiles without one, next number
+  int32_t hstat[2] = {0, 0};
+  auto pack = [&](int cap, bool again) -> int {
+    if (d == 2)
+      hipLaunchKernelGGL(k_tile_pack<2>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk,
+                         g->gcnt, cap, again, stat);
+    else
+      hipLaunchKernelGGL(k_tile_pack<3>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk,
+                         g->gcnt, cap, again, stat);
+    PC_HIP_CHECK(hipGetLastError());
+    PC_HIP_CHECK(hipMemcpyAsync(hstat, stat, 8, hipMemcpyDeviceToHost, s));
+    return PC_OK;
+  };
+  const int cap = list_nodes(d, k_grid, ntile);
+  if (g->gfit)
+    PC_TRY(pack(cap, false));
   else
-    hipLaunchKernelGGL(k_tile_pack<3>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gblk, g->gcnt,
-                       gmax);
-  PC_HIP_CHECK(hipGetLastError());
-  PC_HIP_CHECK(hipMemcpyAsync(&g->gmax, gmax, 4, hipMemcpyDeviceToHost, s));
+    PC_HIP_CHECK(hipMemsetAsync(g->gcnt, 0xff, (size_t)ntile * 4, s));
 
   // boundary + virtual node list (ascending)
   std::vector<uint8_t> hkind((size_t)M);
@@ -1642,6 +1680,25 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   std::vector<uint8_t> hflag((size_t)G);
   PC_HIP_CHECK(hipMemcpyAsync(hflag.data(), nflag, (size_t)G, hipMemcpyDeviceToHost, s));
   PC_HIP_CHECK(hipStreamSynchronize(s));
+  // tiles without a list: longer lists where they are many, else coefficients
+  if (hstat[1] > ntile / LIST_SHARE && cap < tile_cap(d, k_grid)) {
+    PC_TRY(fill_zero(stat + 1, 4, s));
+    PC_TRY(pack(tile_cap(d, k_grid), true));
+    PC_HIP_CHECK(hipStreamSynchronize(s));
+  }
+  g->gmax = hstat[0];
+  g->gover_n = hstat[1];
+  if (g->gover_n) {
+    PC_TRY(dev_alloc((void**)&g->gover, (size_t)g->gover_n * d * k_grid * TP * 8,
+                     "tile coefficients"));
+    hipLaunchKernelGGL(k_tile_number, dim3(nblocks(ntile, 256)), dim3(256), 0, s, g->gcnt, ntile,
+                       stat + 2);
+    if (d == 2)
+      hipLaunchKernelGGL(k_tile_coefs<2>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gover);
+    else
+      hipLaunchKernelGGL(k_tile_coefs<3>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gover);
+    PC_HIP_CHECK(hipGetLastError());
+  }
   std::vector<int32_t> hnear;
   int near_w = 0;
   int64_t near_entries = 0;
@@ -1708,8 +1765,9 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
     PC_HIP_CHECK(hipGetLastError());
   }
   PC_HIP_CHECK(hipStreamSynchronize(s));
-  g->bytes = geom_bytes_for(d, P->n, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near, g->near_w, want64, want32,
-                            k_self, g->n_v);
+  g->bytes = geom_bytes_for(d, P->n, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near,
+                            g->near_w, want64, want32, k_self, g->n_v) +
+             g->gover_n * d * k_grid * TP * 8;
   return PC_OK;
 }
 

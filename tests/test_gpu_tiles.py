@@ -1,6 +1,7 @@
 """The divergence from rows and tile node lists where its dispatch changes: a
-shape parameter beyond the range of the unclamped weight, and the tile shapes
-of thin and short grids."""
+shape parameter beyond the range of the unclamped weight, the tile shapes of
+thin and short grids, and clouds refined in places, whose dense tiles hold more
+nodes than a list and keep coefficients."""
 import numpy as np
 import pytest
 
@@ -98,3 +99,68 @@ def test_thin_grids_hold_no_padding(pc, n, m):
         plan = pc.Plan(len(n), g, (0.125,) * len(n))
         size.append(pc.geom_footprint(plan, int(np.prod(n)), 0, 0, 16, 16 if len(n) == 2 else 27)[0])
     assert size[0] == size[1]
+
+
+def tile_nodes(n, idx, shape):
+    """Distinct nodes of every tile of `shape` points (idx [G, k], x fastest)."""
+    c = np.stack(np.unravel_index(np.arange(idx.shape[0]), n[::-1])[::-1], 1) // np.asarray(shape)
+    tile = np.zeros(idx.shape[0], np.int64)
+    for a in reversed(range(len(n))):
+        tile = tile * (-(-n[a] // shape[a])) + c[:, a]
+    key = np.unique(tile[:, None] * (idx.max() + 1) + idx)
+    return np.bincount(key // (idx.max() + 1))
+
+
+@pytest.mark.parametrize("d,bc,kg", [(2, (PER, N), 32), (2, (N, N), 27), (3, (N, PER, N), 27),
+                                     (3, (N, N, N), 20)],
+                         ids=["2d_periodic", "2d", "3d_periodic", "3d"])
+def test_tiles_without_a_list(pc, d, bc, kg):
+    """A cloud of ordinary density, refined in one corner: the tiles there hold
+    more nodes than the longest list (2048 or 1365)."""
+    n = (64, 24) if d == 2 else (16, 16, 16)
+    h = 1.0 / n[0]
+    grid = Grid(d, n, (h,) * d, bc)
+    x = inputs.jittered_lattice(n, (h,) * d, 8, 0.3)
+    fine = inputs.jittered_lattice((32 * 4, 8 * 4) if d == 2 else (32, 12, 12),
+                                   (h / (4 if d == 2 else 2),) * d, 9, 0.3)
+    corner = np.array([32, 8] if d == 2 else [16, 6, 6])[:, None] * h
+    x = np.concatenate([x[:, ~(x < corner).all(0)], fine], axis=1)
+    assert x.shape[1] <= (5 if d == 2 else 2) * grid.G  # rows are kept
+    kind = np.zeros(x.shape[1], np.uint8)
+    kind[::11] = inputs.KIND_B
+    st = P.build_stencils(grid, x.T.copy(), kind, kg, 16 if d == 2 else 27)
+    nodes = tile_nodes(n, st.grid_idx, (32, 8) if d == 2 else (16, 4, 4))
+    assert nodes.max() > (2048 if d == 2 else 1365) and nodes.min() < 853
+    # nodes a quarter or half a spacing apart under a support of three: the
+    # normal matrices' rounding is about (3 / 0.8)^4 = 200 times the usual
+    geom = check_divergence(pc, n, h, bc, x, kind, kg, tol=1e-11)
+    assert geom.bytes > 0
+
+
+def test_dense_tiles_of_a_large_grid(pc):
+    """More than 2048 3D tiles, few of them with more than 853 nodes: these keep
+    coefficients, as the geometry's size shows, and the divergence is that of
+    the exported coefficients."""
+    import torch
+    n, h, k = (144, 64, 64), 1.0 / 64, 27
+    G = int(np.prod(n))
+    x = inputs.jittered_lattice(n, (h,) * 3, 8, 0.3)
+    fine = inputs.jittered_lattice((24, 12, 12), (h * 2 / 3,) * 3, 9, 0.3)
+    corner = np.array([16, 8, 8])[:, None] * h
+    x = np.concatenate([x[:, ~(x < corner).all(0)], fine], axis=1)
+    kind = np.zeros(x.shape[1], np.uint8)
+    plan = pc.Plan(3, n, (h,) * 3)
+    geom = pc.wls_build(plan, torch.from_numpy(x).cuda(), torch.from_numpy(kind).cuda(), k, 27)
+    gi = torch.empty((k, G), dtype=torch.int32, device="cuda")
+    gc = torch.empty((3, k, G), dtype=torch.float64, device="cuda")
+    pc.geom_export(geom, gi, gc)
+    nodes = tile_nodes(n, to_np(gi).T.astype(np.int64), (16, 4, 4))
+    dense = int((nodes > 853).sum())
+    assert nodes.size > 2048 and 0 < dense <= nodes.size // 16 and nodes.max() <= 1365
+    held = pc.geom_footprint(plan, x.shape[1], 0, 0, k, 27)[0]
+    assert geom.bytes - held == dense * 3 * k * 256 * 8
+    u = torch.randn(3, x.shape[1], dtype=torch.float64, device="cuda")
+    b = torch.empty(G, dtype=torch.float64, device="cuda")
+    pc.div_to_grid(geom, u, b)
+    ref = (gc * u[:, gi.long()]).sum((0, 1))
+    assert rel_l2(to_np(b), to_np(ref)) <= 1e-14
