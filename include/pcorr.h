@@ -369,9 +369,9 @@ int pc_geom_export(const pc_geom* geom, int32_t* grid_idx_dev, double* grid_coef
  *                    at once (cell lists, flags);
  *   ws_bytes[3]      pc_workspace_bytes of a workspace for PC_F64, PC_F32,
  *                    PC_MIXED on that geometry.
- * A cloud refined in places holds more: a tile of 256 grid points whose
- * stencils use more than about 850 (3D) or 2000 (2D) nodes also keeps its
- * coefficients, 8 d k_grid bytes a grid point.
+ * M above the number of grid points adds an allowance for clouds refined in
+ * places, whose densest parts keep coefficients as well (the geometry takes
+ * what it needs of it).
  * Any output pointer may be NULL.  Host only. */
 int pc_geom_footprint(const pc_plan* plan, int64_t M, int64_t n_ib, int64_t n_near,
                       const pc_wls_opts* opts, int64_t* geom_bytes, int64_t* build_peak_bytes,

@@ -105,8 +105,9 @@ struct pc_geom {
   int32_t* gblk;   // [ntile][k_grid * TP]
   int32_t* gcnt;   // [ntile]
   int gmax;        // most nodes of a tile's list
-  int64_t gover_n; // tiles without a list (cnt < 0)
-  double* gover;   // [gover_n][d * k_grid][TP]: their coefficients, or null
+  int64_t gover_n; // tiles that keep coefficients instead of a list (cnt < 0)
+  double* gover;   // [gover_n][d * k_grid][TP], or null
+  bool ggather;    // there are tiles with neither
   double* grow;    // [ntile][grid_rows(d)][TP] or null
   double* gcoef;   // [ntile][d * k_grid][TP] or null
   float* gcoef32;  // or null

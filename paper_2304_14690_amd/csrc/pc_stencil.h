@@ -294,7 +294,8 @@ constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
 // word, [ceil(k/2)][TP], then the list.  A tile with more nodes than a list
 // may hold (a cloud refined there) keeps its coefficients, in float64: its
 // block holds the node indices, [k][TP], and its count is the complement of
-// its place in GridFit.over.
+// its place in GridFit.over; from GridFit.nover on there are none, and every
+// entry's position and value are gathered from memory.
 constexpr int TILE_LOG = 8;
 constexpr int tile_points(int) { return 1 << TILE_LOG; }
 
@@ -362,7 +363,8 @@ struct GridFit {
   const int32_t* blk;      // [ntile][k * TP] words
   const int32_t* cnt;      // [ntile] nodes of the tile's list, or -1
   const double* rows;      // [ntile][grid_rows(d)][TP], or null: stored coefficients
-  const double* over;      // [][d * k][TP]: coefficients of tiles without a list
+  const double* over;      // [nover][d * k][TP]: coefficients of tiles without a list
+  int32_t nover;
   const double* c64;       // [ntile][d * k][TP] (component a, entry i at a * k + i)
   const float* c32;        // or null
   const double* x;         // [d][ms] node positions
@@ -372,6 +374,19 @@ struct GridFit {
 // few nodes between grid points: its tiles outgrow their LDS lists from about
 // 6 G (2D) or 2.4 G (3D) nodes on, and it streams stored coefficients.
 inline bool grid_rows_kept(int d, int64_t G, int64_t M) { return M <= (d == 2 ? 5 : 2) * G; }
+
+// Tiles that may keep coefficients: the sizes known before a build bound what it
+// takes, so they are bounded by the nodes beyond one a grid point.  A 2D tile
+// over its list has about 1250 of these, a 3D one over LIST_NODES 50 to 250 and
+// one over the longest list 500 or more (tiles next to it some less; surface
+// points alone, up to 1 in 32, do not fill one).
+inline int64_t over_tiles(int d, int64_t ntile, int64_t G, int64_t M) {
+  const bool large = d == 3 && ntile > LIST_TILES;
+  const int64_t extra = M - G - (d == 3 && !large ? G / 32 : 0);
+  if (extra <= 0 || !grid_rows_kept(d, G, M)) return 0;
+  const int64_t t = extra / (d == 2 ? 1024 : (large ? 64 : 213));
+  return t < ntile ? t : ntile;
+}
 
 GridFit grid_fit_args(const pc_geom* g);
 inline int64_t grid_tiles(int d, const int32_t* n) { return tile_shape(d, n).tiles(n); }

@@ -57,6 +57,7 @@ GridFit grid_fit_args(const pc_geom* g) {
   A.cnt = g->gcnt;
   A.rows = g->grow;
   A.over = g->gover;
+  A.nover = (int32_t)g->gover_n;
   A.c64 = g->gcoef;
   A.c32 = g->gcoef32;
   A.x = g->xyz;
@@ -145,7 +146,8 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_stored(GridFit A,
 // four) take 2.78 and 2.73 ms against 2.63, 8 x 4 x 4 2.87; sweeping the tiles
 // in slabs along y, so that an XCD's L2 holds the planes tiles share, changes
 // nothing (2.72-2.78).
-template <typename T, int D, int K, bool PER, bool CLAMP>
+// GATHER: for geometries with tiles that have neither list nor coefficients.
+template <typename T, int D, int K, bool PER, bool CLAMP, bool GATHER = false>
 __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* __restrict__ v,
                                                             int64_t M, T* __restrict__ b, int cap) {
   constexpr int TP = tile_points(D);
@@ -183,25 +185,29 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
   }
   double xt[D], acc = 0.0;
   P.position(A, xt);
+  auto entry = [&](const double (&f)[2 * D]) {
+    double x[D], t[D], c[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) x[a] = f[a];
+    grid_offset<D, PER>(A, x, xt, t);
+    row_poly<D>(R, t, c);
+    double s = c[0] * f[D];
+#pragma unroll
+    for (int a = 1; a < D; ++a) s = __builtin_fma(c[a], f[D + a], s);
+    acc = __builtin_fma(row_weight<D, CLAMP>(R, t), s, acc);
+  };
   __syncthreads();
   if (!P.inside(A)) return;
   if (n >= 0) {
     auto place = [&](uint32_t l) {
-      double f[2 * D], x[D], t[D], c[D];
+      double f[2 * D];
 #pragma unroll
       for (int a = 0; a < D; ++a) {
         const double2 q = *reinterpret_cast<const double2*>(node + l + a * pair);
         f[2 * a] = q.x;
         f[2 * a + 1] = q.y;
       }
-#pragma unroll
-      for (int a = 0; a < D; ++a) x[a] = f[a];
-      grid_offset<D, PER>(A, x, xt, t);
-      row_poly<D>(R, t, c);
-      double s = c[0] * f[D];
-#pragma unroll
-      for (int a = 1; a < D; ++a) s = __builtin_fma(c[a], f[D + a], s);
-      acc = __builtin_fma(row_weight<D, CLAMP>(R, t), s, acc);
+      entry(f);
     };
     if constexpr (KU > 0) {
 #pragma unroll
@@ -212,6 +218,17 @@ __global__ void __launch_bounds__(tile_points(D)) k_div_all(GridFit A, const T* 
         const uint32_t wi = (uint32_t)ldnt(blk + (i / 2) * TP + P.t);
         place((i & 1) ? wi >> 16 : wi & 0xffffu);
       }
+    }
+  } else if (GATHER && ~n >= A.nover) {
+    for (int i = 0; i < k; ++i) {
+      const int64_t j = ldnt(blk + i * TP + P.t);
+      double f[2 * D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        f[a] = A.x[a * A.ms + j];
+        f[D + a] = (double)v[a * M + j];
+      }
+      entry(f);
     }
   } else {
     const double* const c = A.over + (int64_t)~n * (D * k * TP) + P.t;
@@ -919,7 +936,10 @@ int launch_div_all(const pc_geom* g, const T* v, T* b, hipStream_t s) {
   const size_t lds = (size_t)g->gmax * g->d * 16;
 #define DIVL(D, K)                                                                             \
   do {                                                                                         \
-    if (gf.clamp)                                                                              \
+    if (g->ggather)                                                                            \
+      hipLaunchKernelGGL((k_div_all<T, D, 0, true, true, true>), grid, block, lds, s, gf, v,    \
+                         g->M, b, g->gmax);                                                    \
+    else if (gf.clamp)                                                                         \
       hipLaunchKernelGGL((k_div_all<T, D, K, true, true>), grid, block, lds, s, gf, v, g->M, b, \
                          g->gmax);                                                             \
     else if (g->per)                                                                           \

@@ -1119,7 +1119,7 @@ __global__ void __launch_bounds__(tile_points(D)) k_tile_coefs(GridFit A, double
   constexpr int TP = tile_points(D);
   const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
   const int32_t n = A.cnt[P.tile];
-  if (n >= 0 || !P.inside(A)) return;
+  if (n >= 0 || ~n >= A.nover || !P.inside(A)) return;
   double xt[D], c[D];
   P.position(A, xt);
   double* const out = over + (int64_t)~n * (D * A.k * TP) + P.t;
@@ -1340,9 +1340,10 @@ struct Scratch {
 
 // Device bytes held by a geometry with these counts (the arrays of
 // pc_wls_build; the node permutation of PC_ORDER_CELL not included).
-int64_t geom_bytes_for(int d, const int32_t* n, int64_t G, int64_t M, int k_grid, int bn, bool fit, int64_t n_ib,
-                       int64_t n_near, int near_w, bool want64, bool want32, int k_self,
-                       int64_t n_v) {
+// over: the tiles that keep coefficients (over_tiles before the build).
+int64_t geom_bytes_for(int d, const int32_t* n, int64_t G, int64_t M, int k_grid, int bn,
+                       bool fit, int64_t n_ib, int64_t n_near, int near_w, bool want64,
+                       bool want32, int k_self, int64_t n_v, int64_t over) {
   const int64_t ms = (M + 63) / 64 * 64, ibs = (n_ib + 63) / 64 * 64;
   const int64_t ell = n_near ? (int64_t)near_w * ((n_near + 63) / 64 * 64) : 0;
   // indices, bases and lists (every geometry)
@@ -1352,6 +1353,7 @@ int64_t geom_bytes_for(int d, const int32_t* n, int64_t G, int64_t M, int k_grid
                   n_ib * 4 + (int64_t)k_self * ms * 4 + n_v * 4;
   // grid rows and positions, float64 in every geometry
   bytes += (rows ? (int64_t)grid_rows(d) * GT * 8 : 0) + (int64_t)d * (ms + (fit ? ibs : 0)) * 8;
+  bytes += over * d * k_grid * tile_points(d) * 8;
   // coefficients, per kept precision (s bytes a value)
   for (int s : {8, 4}) {
     if (!(s == 8 ? want64 : want32)) continue;
@@ -1681,22 +1683,25 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   PC_HIP_CHECK(hipMemcpyAsync(hflag.data(), nflag, (size_t)G, hipMemcpyDeviceToHost, s));
   PC_HIP_CHECK(hipStreamSynchronize(s));
   // tiles without a list: longer lists where they are many, else coefficients
-  if (hstat[1] > ntile / LIST_SHARE && cap < tile_cap(d, k_grid)) {
+  const int64_t over = over_tiles(d, ntile, G, M);
+  if (hstat[1] > std::min(over, ntile / LIST_SHARE) && cap < tile_cap(d, k_grid)) {
     PC_TRY(fill_zero(stat + 1, 4, s));
     PC_TRY(pack(tile_cap(d, k_grid), true));
     PC_HIP_CHECK(hipStreamSynchronize(s));
   }
   g->gmax = hstat[0];
-  g->gover_n = hstat[1];
+  g->gover_n = std::min<int64_t>(hstat[1], over);
+  g->ggather = hstat[1] > over;
   if (g->gover_n) {
+    const GridFit of = grid_fit_args(g);
     PC_TRY(dev_alloc((void**)&g->gover, (size_t)g->gover_n * d * k_grid * TP * 8,
                      "tile coefficients"));
     hipLaunchKernelGGL(k_tile_number, dim3(nblocks(ntile, 256)), dim3(256), 0, s, g->gcnt, ntile,
                        stat + 2);
     if (d == 2)
-      hipLaunchKernelGGL(k_tile_coefs<2>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gover);
+      hipLaunchKernelGGL(k_tile_coefs<2>, dim3((unsigned)ntile), dim3(TP), 0, s, of, g->gover);
     else
-      hipLaunchKernelGGL(k_tile_coefs<3>, dim3((unsigned)ntile), dim3(TP), 0, s, gf, g->gover);
+      hipLaunchKernelGGL(k_tile_coefs<3>, dim3((unsigned)ntile), dim3(TP), 0, s, of, g->gover);
     PC_HIP_CHECK(hipGetLastError());
   }
   std::vector<int32_t> hnear;
@@ -1766,8 +1771,7 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   }
   PC_HIP_CHECK(hipStreamSynchronize(s));
   g->bytes = geom_bytes_for(d, P->n, G, M, k_grid, bn, g->fit != 0, g->n_ib, g->n_near,
-                            g->near_w, want64, want32, k_self, g->n_v) +
-             g->gover_n * d * k_grid * TP * 8;
+                            g->near_w, want64, want32, k_self, g->n_v, g->gover_n);
   return PC_OK;
 }
 
@@ -1899,8 +1903,9 @@ int pc_geom_footprint(const pc_plan* P, int64_t M, int64_t n_ib, int64_t n_near,
   // the near table is as wide as the most B+V entries of a near point: at
   // most k_grid, rounded up to the kernel's widths
   const int near_w = k_grid <= 8 ? 8 : (k_grid <= 16 ? 16 : (k_grid <= 27 && d == 3 ? 27 : 32));
-  const int64_t gb = geom_bytes_for(d, P->n, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64, want32,
-                                    k_self, n_ib) + (cell ? M * 4 : 0);
+  const int64_t gb = geom_bytes_for(
+      d, P->n, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64,
+      want32, k_self, n_ib, over_tiles(d, grid_tiles(d, P->n), P->G, M)) + (cell ? M * 4 : 0);
   if (geom_bytes) *geom_bytes = gb;
   if (build_peak_bytes) *build_peak_bytes = gb + build_scratch_bytes(d, P->G, M, cell);
   if (ws_bytes) {

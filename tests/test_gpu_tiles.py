@@ -111,30 +111,47 @@ def tile_nodes(n, idx, shape):
     return np.bincount(key // (idx.max() + 1))
 
 
-@pytest.mark.parametrize("d,bc,kg", [(2, (PER, N), 32), (2, (N, N), 27), (3, (N, PER, N), 27),
-                                     (3, (N, N, N), 20)],
-                         ids=["2d_periodic", "2d", "3d_periodic", "3d"])
-def test_tiles_without_a_list(pc, d, bc, kg):
-    """A cloud of ordinary density, refined in one corner: the tiles there hold
-    more nodes than the longest list (2048 or 1365)."""
-    n = (64, 24) if d == 2 else (16, 16, 16)
-    h = 1.0 / n[0]
-    grid = Grid(d, n, (h,) * d, bc)
-    x = inputs.jittered_lattice(n, (h,) * d, 8, 0.3)
+def refined(n, h, sparse):
+    """A cloud of ordinary density, or sparse nodes, refined in one corner."""
+    d = len(n)
+    e = 1.5 if sparse else 1.0
+    x = inputs.jittered_lattice(tuple(int(v / e) for v in n), tuple(
+        v * h / int(v / e) for v in n), 8, 0.3)
     fine = inputs.jittered_lattice((32 * 4, 8 * 4) if d == 2 else (32, 12, 12),
                                    (h / (4 if d == 2 else 2),) * d, 9, 0.3)
     corner = np.array([32, 8] if d == 2 else [16, 6, 6])[:, None] * h
-    x = np.concatenate([x[:, ~(x < corner).all(0)], fine], axis=1)
-    assert x.shape[1] <= (5 if d == 2 else 2) * grid.G  # rows are kept
-    kind = np.zeros(x.shape[1], np.uint8)
+    return np.concatenate([x[:, ~(x < corner).all(0)], fine], axis=1)
+
+
+@pytest.mark.parametrize("n,bc,kg,sparse", [
+    ((64, 24), (PER, N), 32, False), ((64, 24), (N, N), 27, False),
+    ((16, 16, 16), (N, PER, N), 27, False), ((32, 16, 16), (N, N, N), 20, False),
+    ((128, 48), (N, PER), 16, True), ((128, 48), (N, N), 32, True),
+    ((24, 16, 16), (PER, N, N), 27, True), ((24, 16, 16), (N, N, N), 32, True),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) and isinstance(v[0], int) else None)
+def test_tiles_without_a_list(pc, n, bc, kg, sparse):
+    """The refined tiles hold more nodes than the longest list (2048 or 1365).
+    With fewer nodes than grid points in all (sparse) nothing is allowed for
+    their coefficients and their entries are gathered."""
+    d, h = len(n), 1.0 / n[0]
+    grid = Grid(d, n, (h,) * d, bc)
+    x = refined(n, h, sparse)
+    G, M = grid.G, x.shape[1]
+    assert M <= (5 if d == 2 else 2) * G  # rows are kept
+    kind = np.zeros(M, np.uint8)
     kind[::11] = inputs.KIND_B
     st = P.build_stencils(grid, x.T.copy(), kind, kg, 16 if d == 2 else 27)
     nodes = tile_nodes(n, st.grid_idx, (32, 8) if d == 2 else (16, 4, 4))
     assert nodes.max() > (2048 if d == 2 else 1365) and nodes.min() < 853
+    allowed = max(0, M - G) // 1024 if d == 2 else max(0, M - G - G // 32) // 213
+    assert (allowed == 0) == sparse
     # nodes a quarter or half a spacing apart under a support of three: the
     # normal matrices' rounding is about (3 / 0.8)^4 = 200 times the usual
     geom = check_divergence(pc, n, h, bc, x, kind, kg, tol=1e-11)
-    assert geom.bytes > 0
+    plan = pc.Plan(d, n, (h,) * d, bc=bc)
+    held = pc.geom_footprint(plan, M, geom.n_ib, geom.n_near, kg, 16 if d == 2 else 27,
+                             want_f32=True)[0]
+    assert geom.bytes <= held
 
 
 def test_dense_tiles_of_a_large_grid(pc):
@@ -148,18 +165,20 @@ def test_dense_tiles_of_a_large_grid(pc):
     fine = inputs.jittered_lattice((24, 12, 12), (h * 2 / 3,) * 3, 9, 0.3)
     corner = np.array([16, 8, 8])[:, None] * h
     x = np.concatenate([x[:, ~(x < corner).all(0)], fine], axis=1)
-    kind = np.zeros(x.shape[1], np.uint8)
+    M = x.shape[1]
+    kind = np.zeros(M, np.uint8)
     plan = pc.Plan(3, n, (h,) * 3)
     geom = pc.wls_build(plan, torch.from_numpy(x).cuda(), torch.from_numpy(kind).cuda(), k, 27)
     gi = torch.empty((k, G), dtype=torch.int32, device="cuda")
     gc = torch.empty((3, k, G), dtype=torch.float64, device="cuda")
     pc.geom_export(geom, gi, gc)
     nodes = tile_nodes(n, to_np(gi).T.astype(np.int64), (16, 4, 4))
-    dense = int((nodes > 853).sum())
-    assert nodes.size > 2048 and 0 < dense <= nodes.size // 16 and nodes.max() <= 1365
-    held = pc.geom_footprint(plan, x.shape[1], 0, 0, k, 27)[0]
-    assert geom.bytes - held == dense * 3 * k * 256 * 8
-    u = torch.randn(3, x.shape[1], dtype=torch.float64, device="cuda")
+    dense, allowed = int((nodes > 853).sum()), (M - G) // 64
+    assert nodes.size > 2048 and 0 < dense <= min(allowed, nodes.size // 16)
+    assert nodes.max() <= 1365
+    held = pc.geom_footprint(plan, M, 0, 0, k, 27)[0]
+    assert held - geom.bytes == (allowed - dense) * 3 * k * 256 * 8
+    u = torch.randn(3, M, dtype=torch.float64, device="cuda")
     b = torch.empty(G, dtype=torch.float64, device="cuda")
     pc.div_to_grid(geom, u, b)
     ref = (gc * u[:, gi.long()]).sum((0, 1))
