@@ -61,7 +61,7 @@ GridFit grid_fit_args(const pc_geom* g) {
   A.c64 = g->gcoef;
   A.c32 = g->gcoef32;
   A.x = g->xyz;
-  const TileShape ts = tile_shape(d, g->n);
+  const TileShape ts = tile_shape(d, g->n, g->gfit);
   const int lt[3] = {ts.lx, ts.ly, ts.lz};
   A.lx = ts.lx;
   A.ly = ts.ly;

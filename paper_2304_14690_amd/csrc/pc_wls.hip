@@ -1347,8 +1347,8 @@ int64_t geom_bytes_for(int d, const int32_t* n, int64_t G, int64_t M, int k_grid
   const int64_t ms = (M + 63) / 64 * 64, ibs = (n_ib + 63) / 64 * 64;
   const int64_t ell = n_near ? (int64_t)near_w * ((n_near + 63) / 64 * 64) : 0;
   // indices, bases and lists (every geometry)
-  const int64_t ntile = grid_tiles(d, n), GT = ntile * tile_points(d);
   const bool rows = grid_rows_kept(d, G, M);
+  const int64_t ntile = grid_tiles(d, n, rows), GT = ntile * tile_points(d);
   int64_t bytes = (int64_t)k_grid * GT * 4 + ntile * 4 + M * 4 + n_ib * 4 + n_near * 4 + ell * 4 +
                   n_ib * 4 + (int64_t)k_self * ms * 4 + n_v * 4;
   // grid rows and positions, float64 in every geometry
@@ -1544,12 +1544,12 @@ int build(const pc_plan* P, const double* xyz, const uint8_t* kind, int64_t M,
   PC_HIP_CHECK(hipGetLastError());
 
   // grid-target stencils
-  const int64_t ntile = grid_tiles(d, P->n);
+  g->gfit = grid_rows_kept(d, G, M);
+  const int64_t ntile = grid_tiles(d, P->n, g->gfit);
   const int TP = tile_points(d);
   if (ntile > INT32_MAX) return fail(PC_ERR_UNSUPPORTED_SIZE, "grid tiles");
   PC_TRY(dev_alloc((void**)&g->gblk, (size_t)ntile * k_grid * TP * 4, "grid stencil indices"));
   PC_TRY(dev_alloc((void**)&g->gcnt, (size_t)ntile * 4, "grid tile counts"));
-  g->gfit = grid_rows_kept(d, G, M);
   if (g->gfit) {
     PC_TRY(dev_alloc((void**)&g->grow, (size_t)ntile * grid_rows(d) * TP * 8, "grid stencil rows"));
   } else {
@@ -1905,7 +1905,7 @@ int pc_geom_footprint(const pc_plan* P, int64_t M, int64_t n_ib, int64_t n_near,
   const int near_w = k_grid <= 8 ? 8 : (k_grid <= 16 ? 16 : (k_grid <= 27 && d == 3 ? 27 : 32));
   const int64_t gb = geom_bytes_for(
       d, P->n, P->G, M, k_grid, bn, fit_lines(k_node, bn, m) != 0, n_ib, n_near, near_w, want64,
-      want32, k_self, n_ib, over_tiles(d, grid_tiles(d, P->n), P->G, M)) + (cell ? M * 4 : 0);
+      want32, k_self, n_ib, over_tiles(d, grid_tiles(d, P->n, true), P->G, M)) + (cell ? M * 4 : 0);
   if (geom_bytes) *geom_bytes = gb;
   if (build_peak_bytes) *build_peak_bytes = gb + build_scratch_bytes(d, P->G, M, cell);
   if (ws_bytes) {

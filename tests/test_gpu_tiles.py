@@ -88,6 +88,18 @@ def test_tile_shapes(pc, n, bc):
     check_divergence(pc, n, 0.125, bc, x, kind, 16 if len(n) == 2 else 27)
 
 
+@pytest.mark.parametrize("n,bc,kg", [((34, 10, 8), (N, N, PER), 27), ((32, 12, 10), (N, N, N), 27),
+                                     ((16, 10, 12), (PER, N, N), 20), ((8, 10, 12), (N, N, N), 16)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple)
+                         and isinstance(v[0], int) else None)
+def test_tile_shapes_of_fine_clouds(pc, n, bc, kg):
+    """Clouds of eight nodes a cell keep stored coefficients in tiles of their
+    own shapes (float32: rounded coefficients and k float32 sums)."""
+    h = 0.125
+    x, kind = lattice(n, h, 8, 2)
+    check_divergence(pc, n, h, bc, x, kind, kg, tol32=3 * kg * 2.0 ** -24, delta=h / 2)
+
+
 @pytest.mark.parametrize("n,m", [((8, 64), (64, 8)), ((16, 128), (128, 16)),
                                  ((8, 32, 32), (32, 32, 8))],
                          ids=["8x64", "16x128", "8x32x32"])
