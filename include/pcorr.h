@@ -244,11 +244,11 @@ int pc_set_allocator(pc_alloc_fn alloc, pc_free_fn free_fn, void* user);
  * Laplacian (homogeneous Neumann condition, Eq. 7), and uploads them (plus
  * float32 copies).  n[a] must be even and in [8, 4096], and the grid may
  * hold at most 2^31 - 2 points (flat grid indices are int32; larger grids
- * give PC_ERR_UNSUPPORTED_SIZE).  Powers of two of
- * at least 32 take the register-resident transform kernels; other lengths
- * (such as the 400 x 402 and 280 x 480 grids of Sec. 3) take a mixed-radix
- * kernel staged in LDS whose cost per line grows with the sum of the prime
- * factors of n/2, and the IB iteration then transforms every line.
+ * give PC_ERR_UNSUPPORTED_SIZE).  Powers of two of at least 32, and 200, 400,
+ * 1000 and 2000, have register-resident transform kernels; other lengths
+ * (such as the 402 and the 280 x 480 of the grids of Sec. 3) take a mixed-radix
+ * kernel staged in LDS whose cost per line grows with the prime factors of n/2
+ * above 7.
  * Synchronises `stream`.  Release with pc_plan_destroy. */
 int pc_plan_create(int d, const int32_t* n, const double* h, void* stream, pc_plan** out);
 

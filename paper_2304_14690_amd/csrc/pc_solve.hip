@@ -73,8 +73,10 @@ __device__ __forceinline__ void mixed_bfly(const cplx<TC>* x, cplx<TC>* y, int g
 }
 
 // Whether lines of half length H take a factor of 7 as a direct sum too: float32
-// lines above 512 points, whose results a butterfly with another rounding would
-// move by up to their own rounding noise (the reason is at float_noise).
+// lines above 512 points (of any grid, PC_MIXED included) keep the results they
+// had before there was a butterfly, for the reason at float_noise; the errors
+// against float64 are the same.  It costs 896^2 solves 51 us against 39, 1792 x
+// 1024 56 against 47.
 __host__ __device__ constexpr bool sums7(int H, size_t elem) { return elem == 4 && H > 256; }
 
 // Mixed-radix Stockham FFT of the C lines held in LDS, for any H whose
@@ -375,7 +377,8 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
       }
     }
     __syncthreads();
-    res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
+    res = reinterpret_cast<const TC*>(
+        fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
   } else {
     const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr);
     constexpr int PB = 2 * B + 1;
@@ -428,7 +431,8 @@ __global__ void __launch_bounds__(1024) dct_lines(LineArgs<TC> A) {
         }
       }
       __syncthreads();
-      res = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
+      res = reinterpret_cast<const TC*>(
+          fft_lds_mixed<TC, true, SUM>(zc, zc2, lsc, C, H, A, twl, tid, nthr));
     } else {
       __syncthreads();
 #pragma unroll
@@ -495,9 +499,9 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
       if (i > 0 && i < n - 1) s0[c * ls + NS - i] = v;
     }
     __syncthreads();
-    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(reinterpret_cast<cplx<TC>*>(s0),
-                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
-                                                  tid, nthr);
+    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(
+        reinterpret_cast<cplx<TC>*>(s0), reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl, tid,
+        nthr);
     if (reinterpret_cast<const TC*>(zf) != s0) {
       xs = s0;
       zs = s1;
@@ -557,8 +561,8 @@ __global__ void __launch_bounds__(1024) dct1_lines(LineArgs<TC> A) {
     za[c * lsc + k] = pre_own_per(xk, TC(0), xhk, TC(0), Tb.tN[k]);
   }
   __syncthreads();
-  const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true, SUM>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+  const TC* er = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(
+      za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
   gen_store<TC, TO, ST>(A, G, tid, nthr,
                         [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
@@ -600,9 +604,9 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
       s0[c * ls + i] = gen_load<TC, TI, LD, false>(A, G, in, sub, e, c, i);
     }
     __syncthreads();
-    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(reinterpret_cast<cplx<TC>*>(s0),
-                                                  reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl,
-                                                  tid, nthr);
+    const cplx<TC>* zf = fft_lds_mixed<TC, false, SUM>(
+        reinterpret_cast<cplx<TC>*>(s0), reinterpret_cast<cplx<TC>*>(s1), lsc, C, H, A, twl, tid,
+        nthr);
     if (reinterpret_cast<const TC*>(zf) != s0) {
       xs = s0;
       zs = s1;
@@ -660,8 +664,8 @@ __global__ void __launch_bounds__(1024) rdft_lines(LineArgs<TC> A) {
                                   Tb.tN[k]);
   }
   __syncthreads();
-  const TC* er = reinterpret_cast<const TC*>(
-      fft_lds_mixed<TC, true, SUM>(za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
+  const TC* er = reinterpret_cast<const TC*>(fft_lds_mixed<TC, true, SUM>(
+      za, reinterpret_cast<cplx<TC>*>(xs), lsc, C, H, A, twl, tid, nthr));
   gen_store<TC, TO, ST>(A, G, tid, nthr,
                         [&](int c, int i) { return er[c * ls + i] * A.outscale; });
 }
@@ -871,11 +875,15 @@ bool lds_twiddles(int N, const int* rad, int nrad) {
 
 bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
-// 2D grids with more than 512 points along an axis, in float32: the velocity's
-// own rounding noise, that of the float32 pressure over a spacing, reaches
-// 1e-5 to 3e-5 there, and a plan with another rounding would move results by as
-// much (1024^2: 1.8e-5, 2048^2: 2.8e-5).  Their axes keep the radix-8 and
-// radix-10 plans (and 7 its direct sum), worth 2% (1024^2) and 5% (2048^2).
+// 2D grids with more than 512 points along an axis, in float32, keep the radix-8
+// and radix-10 plans.  The velocity's own rounding noise, that of the float32
+// pressure over a spacing, reaches 1e-5 to 3e-5 there, and a plan with another
+// rounding moves a result by as much (1024^2: 1.8e-5, 2048^2: 2.8e-5), so runs
+// could not be compared across builds.  It is no matter of accuracy (radix 8 ->
+// radix 4, against float64 over 12 right-hand sides: gradient 4.5e-5 -> 3.4e-5 at
+// 1024^2) and costs 1024^2 solves 25.9 us against 24.6 (2048^2 none: 52.6 against
+// 53.5).  The rule sees the element size alone, so PC_MIXED's float32 passes
+// follow it too, whose results would move by 1e-13 (1024^2 119 against 106 us).
 static bool float_noise(const pc_plan* P, size_t elem) {
   return elem == 4 && P->d == 2 && std::max(P->n[0], P->n[1]) > 512;
 }

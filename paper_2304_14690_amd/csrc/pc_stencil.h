@@ -30,7 +30,8 @@ __device__ __forceinline__ double recip(double x) {
 
 // exp(y) for y <= 709 (flushed to exp(-700) below -700): y = k ln 2 + r,
 // |r| <= ln 2 / 2, and a degree-11 polynomial in r (the minimax fit of
-// (exp(r) - 1 - r) / r^2 leaves 1.3e-17 of the result).
+// (exp(r) - 1 - r) / r^2, with its coefficients rounded, leaves 1.6e-17 of the
+// result).
 __device__ __forceinline__ double exp_fast(double y) {
   constexpr double LOG2E = 1.4426950408889634074, MAGIC = 6755399441055744.0;  // 1.5 2^52
   constexpr double LN2 = 6.9314718055994530942e-1, LN2_LO = 2.3190468138462995584e-17;
@@ -285,9 +286,9 @@ __device__ __forceinline__ void block_coef(const NodeFit& A, const BlockFit<D, M
 constexpr int grid_rows(int d) { return d == 2 ? 12 : 28; }
 
 // The grid points are stored by tiles of 256 points (one workgroup each), their
-// shape by the grid (tile_shape).  The stencils of a tile share most of their nodes (1.7
-// distinct ones per point in 2D and 2.9 in 3D against 16 and 27 entries), so
-// a tile keeps the ascending list of its nodes and each stencil entry is a
+// shape by the grid (tile_shape).  The stencils of a tile share most of their
+// nodes (1.6 distinct ones per point in 2D and 2.8 in 3D against 16 and 27
+// entries), so a tile keeps the ascending list of its nodes and each stencil entry is a
 // 16-bit place in that list: a workgroup gathers every node once into LDS and
 // the entries are read from there (a place is the byte offset of its first
 // pair there).  A tile's block of 4 k TP bytes holds the places, two to a
@@ -524,7 +525,8 @@ __device__ __forceinline__ void grid_offset(const GridFit& A, const double (&x)[
 
 // exp(-alpha |t|^2) as 2^y, y = -alpha log2(e) |t|^2 = k + f, |f| <= 1/2: the
 // product is never rounded on its own (both uses are fused), and the degree-11
-// polynomial (the minimax fit of (2^f - 1 - f ln 2) / f^2) leaves 1e-17.
+// polynomial (the minimax fit of (2^f - 1 - f ln 2) / f^2, its coefficients and
+// ln 2 rounded) leaves 2.7e-17.
 // Without CLAMP y must stay above -1022; alpha |t|^2 <= eps, so it does up to
 // eps = 690 (GridFit.clamp; two more operations an entry than without).
 template <int D, bool CLAMP>

@@ -923,7 +923,8 @@ int launch_div_all(const pc_geom* g, const T* v, T* b, hipStream_t s) {
   const dim3 grid((unsigned)((int64_t)gf.nt[0] * gf.nt[1] * gf.nt[2])), block(tile_points(g->d));
   if (!g->gfit) {
     const T* coef = sizeof(T) == 8 ? (const T*)g->gcoef : (const T*)g->gcoef32;
-#define DIVS(D, K) hipLaunchKernelGGL((k_div_stored<T, D, K>), grid, block, 0, s, gf, coef, v, g->M, b)
+#define DIVS(D, K) \
+  hipLaunchKernelGGL((k_div_stored<T, D, K>), grid, block, 0, s, gf, coef, v, g->M, b)
     if (g->d == 2) {
       if (g->k_grid == 16) DIVS(2, 16); else DIVS(2, 0);
     } else {

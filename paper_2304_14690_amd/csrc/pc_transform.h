@@ -1,6 +1,6 @@
 // Line-transform kernels shared by the translation units that instantiate
-// them: the register-resident radix-8, radix-4 and radix-10 transforms of one grid axis, as a
-// cosine transform (homogeneous Neumann condition, Eq. 7) or as a packed
+// them: the register-resident radix-8, radix-4 and radix-10 transforms of one
+// grid axis, as a cosine transform (homogeneous Neumann condition, Eq. 7) or as a packed
 // real Fourier transform (periodic axis), and the argument block of every
 // transform launch.  Included by pc_solve.hip (Neumann axes) and
 // pc_solve_per.hip (periodic axes), which each instantiate rad_launch for

@@ -783,9 +783,9 @@ __global__ void __launch_bounds__(64) k_node_stencils(NodeStencilArgs A) {
 }
 
 // Geometries whose node rows are evaluated from positions (pc_stencil.h): the
-// block corners and the singularity test.  In the order of Eq. 16's terms the pivots of the normal matrix are
-// the squared norms of the products p_i p_j p_k (halved for the squares,
-// scaled by (h / h_t)^(2 (i + j + k))).
+// block corners and the singularity test.  In the order of Eq. 16's terms the
+// pivots of the normal matrix are the squared norms of the products p_i p_j p_k
+// (halved for the squares, scaled by (h / h_t)^(2 (i + j + k))).
 template <int D, int MB>
 __global__ void __launch_bounds__(256) k_node_fit(const double* __restrict__ xyz, int64_t M,
                                                   GridDesc g, NodeFit A,
@@ -1115,7 +1115,8 @@ __global__ void __launch_bounds__(256) k_tile_number(int32_t* __restrict__ cnt, 
 
 // Their coefficients.
 template <int D>
-__global__ void __launch_bounds__(tile_points(D)) k_tile_coefs(GridFit A, double* __restrict__ over) {
+__global__ void __launch_bounds__(tile_points(D)) k_tile_coefs(GridFit A,
+                                                               double* __restrict__ over) {
   constexpr int TP = tile_points(D);
   const TilePoint<D> P = tile_point<D>(A, blockIdx.x, threadIdx.x);
   const int32_t n = A.cnt[P.tile];
@@ -1319,10 +1320,10 @@ unsigned nblocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void geom_free(pc_geom* g) {
   if (!g) return;
-  void* ptrs[] = {g->gblk,   g->gcnt,   g->grow,    g->gover,  g->gcoef,    g->gcoef32,
-                  g->nbase,  g->ncoef,  g->ncoef32, g->ib,     g->near,   g->nslot,   g->ncoefib, g->ncoefib32, g->ibbase,
-                  g->ibcoef, g->ibcoef32, g->sidx,  g->scoef,   g->scoef32,  g->vlist,
-                  g->perm,   g->xyz,    g->ibx};
+  void* ptrs[] = {g->gblk,    g->gcnt,    g->grow,  g->gover,   g->gcoef,     g->gcoef32, g->xyz,
+                  g->nbase,   g->ncoef,   g->ncoef32, g->ib,    g->near,      g->nslot,
+                  g->ncoefib, g->ncoefib32, g->ibbase, g->ibx,  g->ibcoef,    g->ibcoef32,
+                  g->sidx,    g->scoef,   g->scoef32, g->vlist, g->perm};
   for (void* p : ptrs) dev_free(p);
 }
 

@@ -109,7 +109,8 @@ def test_thin_grids_hold_no_padding(pc, n, m):
     size = []
     for g in (n, m):
         plan = pc.Plan(len(n), g, (0.125,) * len(n))
-        size.append(pc.geom_footprint(plan, int(np.prod(n)), 0, 0, 16, 16 if len(n) == 2 else 27)[0])
+        kn = 16 if len(n) == 2 else 27
+        size.append(pc.geom_footprint(plan, int(np.prod(n)), 0, 0, 16, kn)[0])
     assert size[0] == size[1]
 
 
