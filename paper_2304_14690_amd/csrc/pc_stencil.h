@@ -416,7 +416,11 @@ struct TilePoint {
   __device__ __forceinline__ int64_t flat(const GridFit& A) const {
     return ((int64_t)c[2] * A.n[1] + c[1]) * A.n[0] + c[0];
   }
+  // Rounded as in the build of the rows: fused into the offset below, t would
+  // differ from the offset that the rows belong to by 1e-16 of the box, 3e-14 of
+  // a spacing at 280 points.
   __device__ __forceinline__ void position(const GridFit& A, double (&xt)[D]) const {
+#pragma clang fp contract(off)
 #pragma unroll
     for (int a = 0; a < D; ++a) xt[a] = ((double)c[a] + A.off) * A.h[a];
   }
@@ -516,6 +520,7 @@ __device__ __forceinline__ void row_poly(const GridRows<D>& R, const double (&t)
 template <int D, bool PER>
 __device__ __forceinline__ void grid_offset(const GridFit& A, const double (&x)[D],
                                             const double (&xt)[D], double (&t)[D]) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     t[a] = x[a] - xt[a];

@@ -196,3 +196,30 @@ def test_dense_tiles_of_a_large_grid(pc):
     pc.div_to_grid(geom, u, b)
     ref = (gc * u[:, gi.long()]).sum((0, 1))
     assert rel_l2(to_np(b), to_np(ref)) <= 1e-14
+
+
+@pytest.mark.parametrize("n,bc,kg", [((4000, 8), (PER, N), 16), ((4000, 8), (N, N), 16),
+                                     ((4000, 8), (PER, PER), 20), ((4000, 8), (PER, N), 12),
+                                     ((2000, 8, 8), (PER, N, N), 27), ((2000, 8, 8), (N, N, N), 20)],
+                         ids=["2d_per", "2d", "2d_k20_per", "2d_k12_per", "3d_per", "3d_k20"])
+def test_offsets_are_those_of_the_rows(pc, n, bc, kg):
+    """Far from the origin the offset of a node from a grid point keeps the
+    rounding of the grid point's position that the rows were built with.  An
+    offset with that product unrounded is off by up to half an ulp of the box,
+    2e-13 of a spacing at 4000 points (no power of two: its points are rounded),
+    and takes the divergence as far; the rest of either side's rounding is a
+    tenth of that."""
+    x, kind = lattice(n, 1.0 / n[0], 8)
+    d, h = len(n), 1.0 / n[0]
+    import torch
+    grid = Grid(d, n, (h,) * d, bc)
+    st = P.build_stencils(grid, x.T.copy(), kind, kg, 16 if d == 2 else 27)
+    plan = pc.Plan(d, n, (h,) * d, bc=bc)
+    geom = pc.wls_build(plan, torch.from_numpy(x.copy()).cuda(), torch.from_numpy(kind).cuda(),
+                        kg, 16 if d == 2 else 27)
+    u = np.random.Generator(np.random.PCG64(4)).standard_normal(x.shape)
+    b = torch.empty(plan.G, dtype=torch.float64, device="cuda")
+    pc.div_to_grid(geom, torch.from_numpy(u).cuda(), b)
+    e = rel_l2(to_np(b), P.div_to_grid(st, u.T))
+    print("relative difference", e)
+    assert e <= 1e-13
